@@ -32,6 +32,7 @@ struct mfc_grid {
     double *partial = nullptr; // per-block maxima of the wave-speed reduction
     int64_t partial_len = 0;   // its length (the larger of the two producers' grids)
     double *scalars = nullptr; // [0] smax, [1] dt, [2] t, [3] spare
+    double *dt_out = nullptr;  // caller's word for the step size of the step being enqueued (mfc_rk3_step)
     int *flag = nullptr;       // non-physical flag
     float *mlp = nullptr;      // learned indicator parameters (FP32, flat order of mlp.h)
     float logit_tau = 0.0f;    // routing threshold on the indicator's logit
@@ -109,7 +110,9 @@ int launch_rhs_split_raw(const Grid &g, bool fp32, const void *q, void *out, voi
 // wave-speed partial when the step size is computed inside the launch).
 int64_t split_xy_blocks(const Grid &g);
 // Split path: number of wave-speed partials the z pass writes (one per wavefront).
-int64_t split_z_partials(const Grid &g, bool fp32);
+int64_t split_z_partials(const Grid &g);
+// Split path: planes per workgroup of its two kernels for this grid (3D).
+void split_chunks(Grid &g, bool fp32);
 
 // Reduce nblocks partial maxima, set the step size (cfl > 0: from the
 // maxima; else dt) and advance the accumulated time, on the device.

@@ -86,6 +86,7 @@ void make_grid(const mfc_grid_desc &desc, Grid &g)
     g.eps = desc.weno_eps;
     set_kapila(g, desc);
     g.order = desc.recon == MFC_RECON_WENO3 ? 3 : (desc.recon == MFC_RECON_FIRST_ORDER ? 1 : 5);
+    if (g.ndim == 3) split_chunks(g, desc.precision == MFC_FP32_MIXED);
     g.stretched = 0;
     for (int d = 0; d < desc.ndim; d++) g.stretched |= desc.faces[d] != nullptr;
     if (g.stretched) g.dxmin = 1.0;   // the reduction then returns max (|u_d| + c)/dx_d
@@ -252,22 +253,34 @@ __global__ void __launch_bounds__(kReduceThreads) k_wavespeed(Grid g, const T *_
 }
 
 // One block: reduce the partial maxima, then set the step size and advance
-// the accumulated time.  scalars = [smax, dt, t].
-__global__ void __launch_bounds__(kReduceThreads) k_step_begin(const double *__restrict__ partial, int nblocks,
-                                                               double cfl, double dt_fixed, double dxmin,
-                                                               double *__restrict__ scalars)
+// the accumulated time.  scalars = [smax, dt, t].  Sixteen wavefronts with
+// four loads in flight per lane: the launch is the latency of its loads
+// (20480 partials of a 256^3 grid: 27 us with four wavefronts and one load).
+constexpr int kBeginThreads = 1024;
+__global__ void __launch_bounds__(kBeginThreads) k_step_begin(const double *__restrict__ partial, int nblocks,
+                                                              double cfl, double dt_fixed, double dxmin,
+                                                              double *__restrict__ scalars,
+                                                              double *__restrict__ dt_out)
 {
-    __shared__ double red[kReduceThreads / 64];
+    __shared__ double red[kBeginThreads / 64];
     double m = 0.0;
-    if (partial)
-        for (int b = threadIdx.x; b < nblocks; b += blockDim.x) m = __builtin_fmax(m, partial[b]);
+    if (partial) {
+        int b = threadIdx.x;
+        for (; b + 3 * (int)blockDim.x < nblocks; b += 4 * blockDim.x) {
+            double p[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) p[j] = partial[b + j * blockDim.x];
+            m = __builtin_fmax(m, __builtin_fmax(__builtin_fmax(p[0], p[1]), __builtin_fmax(p[2], p[3])));
+        }
+        for (; b < nblocks; b += blockDim.x) m = __builtin_fmax(m, partial[b]);
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = __builtin_fmax(m, __shfl_xor(m, o, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
         double s = red[0];
-        for (int w = 1; w < kReduceThreads / 64; w++) s = __builtin_fmax(s, red[w]);
+        for (int w = 1; w < (int)blockDim.x / 64; w++) s = __builtin_fmax(s, red[w]);
         double dt = dt_fixed;
         if (partial) {
             scalars[0] = s;
@@ -275,14 +288,8 @@ __global__ void __launch_bounds__(kReduceThreads) k_step_begin(const double *__r
         }
         scalars[1] = dt;
         scalars[2] += dt;
+        if (dt_out) *dt_out = dt;   // mfc_rk3_step's dt_used_dev
     }
-}
-
-// The step size the last step took (scalars[1]) into the caller's device
-// word (mfc_rk3_step's dt_used_dev).
-__global__ void k_copy_dt(const double *__restrict__ scalars, double *__restrict__ out)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) *out = scalars[1];
 }
 
 __global__ void k_set_scalars(double *scalars, int *flag, int what)
@@ -381,7 +388,7 @@ int rhs_dispatch(mfc_grid *h, const void *q, const void *q0, void *out, int mode
     // z faces' cells to the boundary pass, whose maxima follow the z kernel's
     if (st == MFC_OK && has_cbc(h))
         st = launch_cbc(h, q, out, mode, dt, dt_dev, s,
-                        zmax ? zmax + split_z_partials(h->g, h->desc.precision == MFC_FP32_MIXED) : nullptr);
+                        zmax ? zmax + split_z_partials(h->g) : nullptr);
     return st;
 }
 
@@ -404,8 +411,9 @@ void fill_ghosts_t(mfc_grid *h, T *q, hipStream_t s)
 
 void launch_step_begin(mfc_grid *h, const double *partial, int nblocks, double cfl, double dt, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(kReduceThreads), 0, s, partial, nblocks, cfl, dt, h->g.dxmin,
-                       h->scalars);
+    const int threads = nblocks > 2048 ? kBeginThreads : 256;
+    hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(threads), 0, s, partial, nblocks, cfl, dt, h->g.dxmin,
+                       h->scalars, h->dt_out);
 }
 
 namespace {
@@ -539,7 +547,7 @@ int mfc_init_grid(const mfc_grid_desc *desc, mfc_grid **out)
     }
     h->partial_len = std::max<int64_t>(
         kReduceBlocks,
-        desc->ndim == 3 ? std::max(split_xy_blocks(g), split_z_partials(g, is_fp32(h)) + cbc_stored_blocks(g)) : 0);
+        desc->ndim == 3 ? std::max(split_xy_blocks(g), split_z_partials(g) + cbc_stored_blocks(g)) : 0);
     alloc((void **)&h->partial, h->partial_len * 8);
     alloc((void **)&h->scalars, 4 * 8);
     alloc((void **)&h->flag, 8);
@@ -669,27 +677,27 @@ bool carries_wavespeed(const mfc_grid *h, double cfl)
 // Number of wave-speed maxima a carrying last stage leaves in h->partial.
 int64_t carried_partials(const mfc_grid *h)
 {
-    return split_z_partials(h->g, is_fp32(h)) + (has_cbc(h) ? cbc_stored_blocks(h->g) : 0);
+    return split_z_partials(h->g) + (has_cbc(h) ? cbc_stored_blocks(h->g) : 0);
 }
 
 // One SSP-RK3 step.  carried_in: the wave-speed partials of q^n are in
 // h->partial (written by the previous step's last stage); carry_out: have
 // this step's last stage write those of q^{n+1}.
-int rk3_step_launches(mfc_grid *h, void *q, double cfl, double dt, double *dt_used_dev, hipStream_t s,
-                      bool carried_in, bool carry_out);
+int rk3_step_launches(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, bool carried_in, bool carry_out);
 
 int rk3_step(mfc_grid *h, void *q, double cfl, double dt, double *dt_used_dev, hipStream_t s, bool carried_in,
              bool carry_out)
 {
     // with a timing stride, only every stride-th step's launches are timed
     h->timing_skip = h->timing && (h->timing_step++ % h->timing_stride) != 0;
-    const int st = rk3_step_launches(h, q, cfl, dt, dt_used_dev, s, carried_in, carry_out);
+    h->dt_out = dt_used_dev;   // written by the step's k_step_begin
+    const int st = rk3_step_launches(h, q, cfl, dt, s, carried_in, carry_out);
+    h->dt_out = nullptr;
     h->timing_skip = false;
     return st;
 }
 
-int rk3_step_launches(mfc_grid *h, void *q, double cfl, double dt, double *dt_used_dev, hipStream_t s,
-                      bool carried_in, bool carry_out)
+int rk3_step_launches(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, bool carried_in, bool carry_out)
 {
     int st = MFC_OK;
     void *A = h->stage_a, *B = h->stage_b;
@@ -718,7 +726,6 @@ int rk3_step_launches(mfc_grid *h, void *q, double cfl, double dt, double *dt_us
     if ((st = rhs_dispatch(h, A, q, B, 2, 0.0, dt_dev, s))) return st;
     if (fill && (st = fill_ghosts(h, B, s))) return st;
     if ((st = rhs_dispatch(h, B, q, q, 3, 0.0, dt_dev, s, 0.0, carry_out ? h->partial : nullptr))) return st;
-    if (dt_used_dev) hipLaunchKernelGGL(k_copy_dt, dim3(1), dim3(64), 0, s, h->scalars, dt_used_dev);
     return hip_status(hipGetLastError(), "rk3 step launch");
 }
 

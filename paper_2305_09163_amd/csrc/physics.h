@@ -38,6 +38,7 @@ struct Grid {
     double g1, g2, h1, h2;
     double eps;       // WENO epsilon
     int bc[6];        // boundary kind per face (x-, x+, y-, y+, z-, z+): MFC_BC_*
+    int xy_planes, z_planes;  // 3D: planes per workgroup of the split path's two kernels
     int order;        // reconstruction of the staged path: 5 WENO5, 3 WENO3, 1 first order
     // Kapila alpha1 equation (kapila != 0): rho_k c_k^2 = zg[k] p + zp[k]
     int kapila;

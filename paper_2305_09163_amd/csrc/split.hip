@@ -1,7 +1,7 @@
 // Split right-hand side (3D): two launches per Runge-Kutta stage.
 //
 //   k_xy  x and y directions of eq. (fvmdis) (Sec. 3.1): a workgroup of
-//         256 threads owns a 16 x 13 tile of an x-y plane and walks four
+//         256 threads owns a 16 x 13 tile of an x-y plane and walks a few
 //         planes; each plane (with 3-cell halos) is converted to primitives
 //         into LDS once, every cell of the tile plus one halo cell per side is
 //         reconstructed once per direction (WENO5, both face values from one
@@ -37,6 +37,7 @@
 // one takes the linear fifth-order stencil for every variable instead of
 // WENO5.  ORDER selects the reconstruction otherwise (5 WENO5, 3 WENO3,
 // 1 first order; the routed variant is always 5).
+#include <cmath>
 #include <type_traits>
 
 #include "charbc.h"
@@ -52,16 +53,13 @@ namespace {
 // face on the reconstruction's + side with its own + value kept in
 // registers, so that only the - values pass through LDS.  With a 16 x 13 tile
 // the FP64 kernel's LDS (primitives, - values, face fluxes: 51.8 KB) admits
-// three workgroups per CU; 16 x 14 needs 54.8 KB and admits two.  Four
-// planes per workgroup (more workgroups) measured faster than 8 or 16.
+// three workgroups per CU; 16 x 14 needs 54.8 KB and admits two.  The planes
+// a workgroup walks are Grid::xy_planes (split_chunks below).
 #ifndef MFC_XY_TX
 #define MFC_XY_TX 16
 #endif
 #ifndef MFC_XY_TY
 #define MFC_XY_TY 13
-#endif
-#ifndef MFC_XY_PLANES
-#define MFC_XY_PLANES 4
 #endif
 constexpr int TX = MFC_XY_TX, TY = MFC_XY_TY, NT = 256, NOWN = TX * TY;
 static_assert(NOWN <= NT, "one thread per tile cell");
@@ -86,20 +84,7 @@ constexpr int NP = NPX > NPY ? NPX : NPY;
 constexpr int NFX = (TX + 2) * (TY - 1) + TX + 1;
 constexpr int NFY = TX * (TY + 1);
 constexpr int NF = NFX > NFY ? NFX : NFY;
-constexpr int kPlanesXY = MFC_XY_PLANES;  // planes per k_xy workgroup
-#ifndef MFC_Z_Y
-#define MFC_Z_Y 4
-#endif
-constexpr int kZX = 64, kZY = MFC_Z_Y;  // k_z workgroup: 64 x 4 columns
-#ifndef MFC_Z_LZ64
-#define MFC_Z_LZ64 16
-#endif
-#ifndef MFC_Z_LZ32
-#define MFC_Z_LZ32 16
-#endif
-// planes per k_z column chunk (the march re-reads 6 halo planes per chunk)
-template <class T>
-constexpr int kLZ = sizeof(T) == 8 ? MFC_Z_LZ64 : MFC_Z_LZ32;
+constexpr int kNZT = 256, kZWavesWG = kNZT / 64;  // k_z workgroup: 256 columns of the x-y plane
 
 #ifndef MFC_XCD
 #define MFC_XCD 1
@@ -261,7 +246,7 @@ __global__ void __launch_bounds__(NT, (kXYWaves<T, ROUTE, STRETCH, KEEP>))
     int bx, by, bz;
     tile_of_block(bx, by, bz);
     const int x0 = bx * TX, y0 = by * TY;
-    const int z0 = bz * kPlanesXY, z1 = min(z0 + kPlanesXY, g.n[2]);
+    const int z0 = bz * g.xy_planes, z1 = min(z0 + g.xy_planes, g.n[2]);
     const int xmax = g.n[0] + H - 1, ymax = g.n[1] + H - 1;
     const int gx = x0 + tx, gy = y0 + ty;
     const bool cell = tid < NOWN;                       // this thread has a tile cell
@@ -557,9 +542,10 @@ __global__ void __launch_bounds__(NT, (kXYWaves<T, ROUTE, STRETCH, KEEP>))
     if (bad) atomicOr(flag, 1);
 }
 
-// z direction + stage update.  Threads of a workgroup own a 64 x 4 block of
-// columns (64 consecutive x per wavefront: coalesced plane loads) and march
-// through kLZ planes, starting two planes early to reconstruct cell z0-1 and
+// z direction + stage update.  Threads of a workgroup own 256 consecutive
+// (x, y) columns, x fastest (a wavefront's plane loads are one or two
+// contiguous runs whatever the row length), and march through
+// Grid::z_planes planes, starting two planes early to reconstruct cell z0-1 and
 // solve face z0-1/2 without writing.  Of the five planes of a column's
 // reconstruction window, the kRing oldest are kept in a per-thread ring in
 // LDS (each thread touches only its own slots: no barriers) and the others in
@@ -611,7 +597,7 @@ static_assert(kRing<false> >= 1 && kRing<false> <= 4 && kRing<true> >= 1 && kRin
 // stored values (the same conversion in the same arithmetic, so the same
 // maxima), one partial maximum per wavefront in smax_partial.
 template <class T, bool ROUTE, int ORDER, bool STRETCH, bool KEEP, bool REREAD, bool SMAX = false>
-__global__ void __launch_bounds__(kZX * kZY, kZWaves<T>)
+__global__ void __launch_bounds__(kNZT, kZWaves<T>)
     k_z(Grid g, const T *__restrict__ q, T *__restrict__ out, const T *__restrict__ lxy, int mode, double dt,
         const double *__restrict__ dt_dev, int *__restrict__ flag, const float *__restrict__ mlpw, float logit_tau,
         T sqrt_eps, double *__restrict__ smax_partial)
@@ -620,33 +606,32 @@ __global__ void __launch_bounds__(kZX * kZY, kZWaves<T>)
     // window of W = 2H - 1 planes; the kRing oldest in the LDS ring
     constexpr int H = kHalo<ORDER>, OFF = kOff<ORDER>, W = 2 * H - 1;
     constexpr int kRing = mfc::kRing<ROUTE> < W - 1 ? mfc::kRing<ROUTE> : W - 1, kZReg = W - kRing;
-    constexpr int NV = 7, A = 6, NZT = kZX * kZY;
+    constexpr int NV = 7, A = 6, NZT = kNZT;
     const T eps = T(g.eps), idz_u = T(g.inv_dx[2]);
     int bx, by, bz;
     tile_of_block(bx, by, bz);
-    int gx = bx * kZX + threadIdx.x % kZX;
-    int gy = by * kZY + threadIdx.x / kZX;
-    const bool own = gx < g.n[0] && gy < g.n[1];
+    const int columns = g.n[0] * g.n[1], col = bx * kNZT + (int)threadIdx.x;
+    const bool own = col < columns;
+    const int cc = min(col, columns - 1);
+    const int gx = cc % g.n[0], gy = cc / g.n[0];
     __shared__ __align__(16) typename std::conditional<ROUTE, mlp::Params, char>::type s_mlp;
     __shared__ __align__(16) uint16_t s_feat[ROUTE ? NZT * 16 : 1];
     __shared__ T s_ring[kRing][NV][NZT];
     if constexpr (ROUTE || SMAX) {
         // every lane of a wavefront takes part in the classification or the
-        // reduction: lanes past a ragged edge march a duplicate of the last
-        // column (their maxima are those of that column)
+        // reduction: lanes past the last column march a duplicate of it
+        // (their maxima are those of that column)
         if constexpr (ROUTE) {
             mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, NZT);
             __syncthreads();
         }
-        gx = min(gx, g.n[0] - 1);
-        gy = min(gy, g.n[1] - 1);
     } else if (!own) {
         return;   // no barriers in this variant
     }
     double smax = 0.0;
     uint16_t *scratch = s_feat + (ROUTE ? (threadIdx.x / 64) * 64 * 16 : 0);
     const int lane = threadIdx.x % 64, t = threadIdx.x;
-    const int z0 = bz * kLZ<T>, z1 = min(z0 + kLZ<T>, g.n[2]);
+    const int z0 = bz * g.z_planes, z1 = min(z0 + g.z_planes, g.n[2]);
     const T hdt = T(mode ? (dt_dev ? *dt_dev : dt) : 0.0);
     const T cb = T(mode == 2 ? 0.25 : (mode == 3 ? 2.0 / 3.0 : 1.0));
     const T sz = mode ? cb * hdt : T(1);   // weight of L_z in the result
@@ -825,14 +810,18 @@ __global__ void __launch_bounds__(kZX * kZY, kZWaves<T>)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) smax = __builtin_fmax(smax, __shfl_xor(smax, o, 64));
         if (lane == 0)
-            smax_partial[((int64_t)(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * kZY + t / 64] = smax;
+            smax_partial[((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * kZWavesWG + t / 64] = smax;
     }
     if (bad) atomicOr(flag, 1);
 }
 
 dim3 xy_grid(const Grid &g)
 {
-    return dim3((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, (g.n[2] + kPlanesXY - 1) / kPlanesXY);
+    return dim3((g.n[0] + TX - 1) / TX, (g.n[1] + TY - 1) / TY, (g.n[2] + g.xy_planes - 1) / g.xy_planes);
+}
+dim3 z_grid(const Grid &g)
+{
+    return dim3((g.n[0] * g.n[1] + kNZT - 1) / kNZT, 1, (g.n[2] + g.z_planes - 1) / g.z_planes);
 }
 
 template <class T, bool ROUTE, int ORDER, bool STRETCH = false, bool KEEP = false>
@@ -841,7 +830,7 @@ int rhs_split(mfc_grid *h, const T *q, const T *q0, T *out, int mode, double dt,
 {
     const Grid &g = h->g;
     const dim3 gxy = xy_grid(g);
-    dim3 gz((g.n[0] + kZX - 1) / kZX, (g.n[1] + kZY - 1) / kZY, (g.n[2] + kLZ<T> - 1) / kLZ<T>);
+    const dim3 gz = z_grid(g);
     T *lxy = (T *)h->lxy;
     const T se = T(__builtin_sqrt(g.eps));
     double *partial = cfl > 0.0 ? h->partial : nullptr;
@@ -857,16 +846,16 @@ int rhs_split(mfc_grid *h, const T *q, const T *q0, T *out, int mode, double dt,
     timing_begin(h, s, 1);
     bool done = false;
     if (zmax && mode != 0 && fold) {
-        hipLaunchKernelGGL((k_z<T, ROUTE, ORDER, STRETCH, KEEP, false, true>), gz, dim3(kZX * kZY), 0, s, g, q, out,
+        hipLaunchKernelGGL((k_z<T, ROUTE, ORDER, STRETCH, KEEP, false, true>), gz, dim3(kNZT), 0, s, g, q, out,
                            lxy, mode, dt, dt_dev, h->flag, h->mlp, h->logit_tau, se, zmax);
         done = true;
     }
     if (done) {
     } else if (mode != 0 && !fold) {
-        hipLaunchKernelGGL((k_z<T, ROUTE, ORDER, STRETCH, KEEP, true>), gz, dim3(kZX * kZY), 0, s, g, q, out, lxy, mode,
+        hipLaunchKernelGGL((k_z<T, ROUTE, ORDER, STRETCH, KEEP, true>), gz, dim3(kNZT), 0, s, g, q, out, lxy, mode,
                            dt, dt_dev, h->flag, h->mlp, h->logit_tau, se, nullptr);
     } else {
-        hipLaunchKernelGGL((k_z<T, ROUTE, ORDER, STRETCH, KEEP, false>), gz, dim3(kZX * kZY), 0, s, g, q, out, lxy, mode,
+        hipLaunchKernelGGL((k_z<T, ROUTE, ORDER, STRETCH, KEEP, false>), gz, dim3(kNZT), 0, s, g, q, out, lxy, mode,
                            dt, dt_dev, h->flag, h->mlp, h->logit_tau, se, nullptr);
     }
     timing_end(h, s, 1);
@@ -881,11 +870,11 @@ template <class T, int ORDER>
 int rhs_split_raw(const Grid &g, const T *q, T *out, T *lxy, int *flag, hipStream_t s)
 {
     const dim3 gxy = xy_grid(g);
-    const dim3 gz((g.n[0] + kZX - 1) / kZX, (g.n[1] + kZY - 1) / kZY, (g.n[2] + kLZ<T> - 1) / kLZ<T>);
+    const dim3 gz = z_grid(g);
     const T se = T(__builtin_sqrt(g.eps));
     hipLaunchKernelGGL((k_xy<T, false, ORDER, false, false>), gxy, dim3(NT), 0, s, g, q, q, lxy, flag, nullptr, 0.f,
                        se, nullptr, 0, 0, 0.0, nullptr);
-    hipLaunchKernelGGL((k_z<T, false, ORDER, false, false, false>), gz, dim3(kZX * kZY), 0, s, g, q, out, lxy, 0, 0.0,
+    hipLaunchKernelGGL((k_z<T, false, ORDER, false, false, false>), gz, dim3(kNZT), 0, s, g, q, out, lxy, 0, 0.0,
                        nullptr, flag, nullptr, 0.f, se, nullptr);
     return hip_status(hipGetLastError(), "split right-hand side launch");
 }
@@ -915,10 +904,52 @@ int64_t split_xy_blocks(const Grid &g)
     return (int64_t)b.x * b.y * b.z;
 }
 
-int64_t split_z_partials(const Grid &g, bool fp32)
+int64_t split_z_partials(const Grid &g)
 {
-    const int lz = fp32 ? kLZ<float> : kLZ<double>;
-    return (int64_t)((g.n[0] + kZX - 1) / kZX) * ((g.n[1] + kZY - 1) / kZY) * ((g.n[2] + lz - 1) / lz) * kZY;
+    const dim3 b = z_grid(g);
+    return (int64_t)b.x * b.z * kZWavesWG;
+}
+
+// Both kernels walk planes serially within a workgroup, so a small grid wants
+// few planes per workgroup (more workgroups side by side) and a large one
+// many (the march re-reads 6 halo planes per chunk; the x+y walk hides a
+// plane's loads behind the previous plane).
+//
+// z pass: a chunk of lz planes costs lz + 4 plane steps (the two cells before
+// it and the first window), each of which takes about 0.75 + 1.05 k us (FP64)
+// or 1 + 0.7 k us (FP32) with k workgroups per CU, k = W / 256 for W
+// workgroups, rounded up while the launch is a few rounds (a last partial
+// round costs a whole one).  The chunk that minimises the product is within
+// 4 % of the best of a sweep of 1 .. 32 planes on every size tried; against
+// the 16 planes that suit 128^3 (FP64): 36 x 34 x 33 35.0 -> 10.7 us (1
+// plane), 64^3 38.8 -> 18.5 (4), 100 x 75 x 61 40.0 -> 27.2 (4), 112^3
+// 63.2 -> 57.9 (8), 128^3 78.2 (16); FP32 256^3 364 -> 341 (32).
+//
+// x+y pass: one plane per workgroup below four rounds of the 768 resident
+// workgroups, two below 10240 plane tiles, else four: 36 x 34 x 33 24.5 ->
+// 13.5 us, 64^3 35.0 -> 26.3, 96 x 80 x 72 47.2 -> 47.0, 128^3 138.1 with four
+// (139 with two, 147 with one), FP32 256^3 584 with four (605, 640).
+//
+// Neither choice changes a cell's arithmetic.  Chunks are kept long enough
+// for the launch's z extent (65535).
+void split_chunks(Grid &g, bool fp32)
+{
+    const int nz = g.n[2];
+    const int64_t tiles = (int64_t)((g.n[0] + TX - 1) / TX) * ((g.n[1] + TY - 1) / TY) * nz;
+    g.xy_planes = nz > 65535 ? 4 : (tiles < 4 * 768 ? 1 : (tiles < 10240 ? 2 : 4));
+    const int64_t cols = ((int64_t)g.n[0] * g.n[1] + kNZT - 1) / kNZT;
+    double best = 1e300;
+    for (int lz = 1; lz <= 32; lz++) {
+        const int64_t chunks = (nz + lz - 1) / lz;
+        if (chunks > 65535) continue;
+        double k = double(cols * chunks) / 256.0;
+        if (k < 4.0) k = std::ceil(k);
+        const double cost = (lz + 4) * (fp32 ? 1.0 + 0.7 * k : 0.75 + 1.05 * k);
+        if (cost < best) {
+            best = cost;
+            g.z_planes = lz;
+        }
+    }
 }
 
 int launch_rhs_split(mfc_grid *h, const void *q, const void *q0, void *out, int mode, double dt,
