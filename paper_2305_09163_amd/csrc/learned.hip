@@ -5,7 +5,7 @@
 // and the handle call that installs a trained network for the routed
 // reconstruction.
 //
-//   k_harvest     one thread per interior (cell, direction): the 15 inputs
+//   k_harvest     one thread per interior cell, every direction: the 15 inputs
 //                 and the label "every variable keeps its WENO5 weights
 //                 within 0.01 of the ideal ones on both faces";
 //   k_mlp_grad    forward + backward over a batch; each wavefront walks
@@ -48,79 +48,139 @@ __device__ __forceinline__ void wave_sync()
 }
 
 // Largest |omega_r - d_r| of WENO5-JS over the three stencils and both faces
-// of the 5-cell stencil s (the weights of Sec. 3.2 with the Jiang-Shu
-// smoothness indicators, written in the divided differences of the stencil).
-__device__ double weno_deviation(const double *s, double eps)
+// of the 5-cell stencil s (the weights of Sec. 3.2).  As in the solver's
+// weno5_pair, e_r = 3/4 (eps + beta_r) in the divided differences of the
+// stencil and omega_r through common denominators (omega_0 ~ 1 (e_1 e_2)^2
+// and so on, ideal weights times ten), which leaves one reciprocal per face;
+// these are refined to the last place.
+__device__ __forceinline__ double weno_deviation(const double *v, int s, double eps)
 {
-#pragma clang fp contract(off)
-    const double dm2 = s[1] - s[0], dm1 = s[2] - s[1], d0 = s[3] - s[2], d1 = s[4] - s[3];
-    double beta[3];
-    beta[0] = (10.0 / 3.0) * dm1 * dm1 - (11.0 / 3.0) * dm1 * dm2 + (4.0 / 3.0) * dm2 * dm2;
-    beta[1] = (4.0 / 3.0) * d0 * d0 - (5.0 / 3.0) * d0 * dm1 + (4.0 / 3.0) * dm1 * dm1;
-    beta[2] = (10.0 / 3.0) * d0 * d0 - (11.0 / 3.0) * d0 * d1 + (4.0 / 3.0) * d1 * d1;
-    const double dp[3] = {0.1, 0.6, 0.3}, dmn[3] = {0.3, 0.6, 0.1};
-    double ap[3], am[3], sp = 0.0, sm = 0.0;
-#pragma unroll
-    for (int r = 0; r < 3; r++) {
-        const double e = (eps + beta[r]) * (eps + beta[r]);
-        ap[r] = dp[r] / e;
-        am[r] = dmn[r] / e;
-        sp += ap[r];
-        sm += am[r];
-    }
-    double dev = 0.0;
-#pragma unroll
-    for (int r = 0; r < 3; r++) {
-        dev = fmax(dev, fabs(ap[r] / sp - dp[r]));
-        dev = fmax(dev, fabs(am[r] / sm - dmn[r]));
-    }
-    return dev;
+    const double b = v[s] - v[0], a = v[2 * s] - v[s], c = v[3 * s] - v[2 * s], d = v[4 * s] - v[3 * s];
+    const double e3 = 0.75 * eps;
+    const double e0 = __builtin_fma(a, __builtin_fma(2.5, a, -2.75 * b), __builtin_fma(b, b, e3));
+    const double e1 = __builtin_fma(c, __builtin_fma(-1.25, a, c), __builtin_fma(a, a, e3));
+    const double e2 = __builtin_fma(c, __builtin_fma(2.5, c, -2.75 * d), __builtin_fma(d, d, e3));
+    const double s0 = e0 * e0, s1 = e1 * e1, s2 = e2 * e2;
+    const double m0 = s1 * s2, m1 = 6.0 * (s0 * s2), m2 = s0 * s1;
+    const double rp = divisor(__builtin_fma(3.0, m2, m0 + m1));   // + face: weights 1, 6, 3
+    const double rm = divisor(__builtin_fma(3.0, m0, m1 + m2));   // - face: weights 3, 6, 1
+    double dev = fmax(fabs(__builtin_fma(m0, rp, -0.1)), fabs(__builtin_fma(m1, rp, -0.6)));
+    dev = fmax(dev, fabs(__builtin_fma(3.0 * m2, rp, -0.3)));
+    dev = fmax(dev, fabs(__builtin_fma(3.0 * m0, rm, -0.3)));
+    dev = fmax(dev, fabs(__builtin_fma(m1, rm, -0.6)));
+    return fmax(dev, fabs(__builtin_fma(m2, rm, -0.1)));
 }
 
+// Harvest tile: 256 cells, one per thread, which forms its cell's samples of
+// every direction.  The tile's primitives with their halos of two cells are
+// converted once into LDS (3D: 768 conversions for 768 samples instead of
+// five per sample); the pressure as the two factors of its product.  Bound by the FP64 issue of the deviations.
 template <int NDIM>
-__global__ void __launch_bounds__(kThreads)
+struct HarvestTile {
+    static constexpr int H = 2, NV = 4 + NDIM;
+    static constexpr int TX = NDIM == 1 ? 256 : (NDIM == 2 ? 16 : 8), TY = NDIM == 1 ? 1 : (NDIM == 2 ? 16 : 8);
+    static constexpr int TZ = NDIM == 3 ? 4 : 1;
+    static constexpr int OY = NDIM >= 2 ? H : 0, OZ = NDIM == 3 ? H : 0;   // LDS position of the first cell
+    static constexpr int PX = TX + 2 * H, PY = TY + 2 * OY, PZ = TZ + 2 * OZ, PLANE = PX * PY * PZ;
+    // halo cells of the x, y and z faces
+    static constexpr int HX = 2 * H * TY * TZ, HY = 2 * OY * TX * TZ, HZ = 2 * OZ * TX * TY;
+    static_assert(TX * TY * TZ == kThreads, "one cell per thread");
+};
+
+// 96^3 cells: 192 us with one thread per (cell, direction), five conversions
+// and 99 IEEE divisions per sample; 89 us so (14 reciprocals).
+template <int NDIM>
+__global__ void __launch_bounds__(kThreads, 2)
     k_harvest(Grid g, const double *__restrict__ q, uint16_t *__restrict__ X, uint8_t *__restrict__ Y,
               double *__restrict__ D, double sqrt_eps, double threshold, int64_t cells)
 {
-    constexpr int NV = 4 + NDIM;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= cells * NDIM) return;
-    const int d = (int)(t / cells);
-    const int64_t c = t % cells;
-    int ijk[3] = {(int)(c % g.n[0]), (int)((c / g.n[0]) % g.n[1]), (int)(c / ((int64_t)g.n[0] * g.n[1]))};
-    double w[5][NV];
-#pragma unroll
-    for (int p = 0; p < 5; p++) {
-        int a[3] = {ijk[0], ijk[1], ijk[2]};
-        a[d] += p - 2;
-        const int64_t o = (int64_t)(a[2] + g.off[2]) * g.stride[2] + (int64_t)(a[1] + g.off[1]) * g.stride[1] +
-                          (a[0] + g.off[0]);
-        double qc[NV];
+    using S = HarvestTile<NDIM>;
+    constexpr int NV = S::NV, H = S::H;
+    constexpr int E = NV - 2, A = NV - 1;
+    __shared__ double s_w[NV][S::PLANE];   // row E: the pressure's first factor
+    __shared__ double s_ig[S::PLANE];      // its second
+    const int tid = threadIdx.x;
+    const int tx = tid % S::TX, ty = (tid / S::TX) % S::TY, tz = tid / (S::TX * S::TY);
+    const int tiles_x = (g.n[0] + S::TX - 1) / S::TX, tiles_y = (g.n[1] + S::TY - 1) / S::TY;
+    const int x0 = blockIdx.x % tiles_x * S::TX, y0 = blockIdx.x / tiles_x % tiles_y * S::TY;
+    const int z0 = blockIdx.x / tiles_x / tiles_y * S::TZ;
+    // position (i, j, k) of the tile's window, from its first interior cell;
+    // those past a ragged tile's last halo load a duplicate that no sample of the grid reads
+    auto stage = [&](int i, int j, int k) {
+        const int x = min(x0 + i, g.n[0] + H - 1), y = min(y0 + j, g.n[1] - 1 + S::OY), z = min(z0 + k, g.n[2] - 1 + S::OZ);
+        const int64_t o = (int64_t)(z + g.off[2]) * g.stride[2] + (int64_t)(y + g.off[1]) * g.stride[1] + (x + g.off[0]);
+        double qc[NV], w[NV], pf[2];
 #pragma unroll
         for (int v = 0; v < NV; v++) qc[v] = q[v * g.vstride + o];
-        (void)cons_to_prim<NDIM, double>(g, qc, w[p]);
-    }
-    double al[5], rh[5], pr[5];
+        (void)cons_to_prim<NDIM, double>(g, qc, w, pf);
+        w[E] = pf[0];
+        const int p = ((k + S::OZ) * S::PY + j + S::OY) * S::PX + i + H;
 #pragma unroll
-    for (int p = 0; p < 5; p++) {
-        al[p] = w[p][NV - 1];
-        rh[p] = w[p][0] + w[p][1];
-        pr[p] = w[p][NV - 2];
+        for (int v = 0; v < NV; v++) s_w[v][p] = w[v];
+        s_ig[p] = pf[1];
+    };
+    stage(tx, ty, tz);
+    for (int h = tid; h < S::HX + S::HY + S::HZ; h += kThreads) {
+        int a, i, j, k;
+        if (h < S::HX) {
+            a = h % (2 * H);
+            j = (h / (2 * H)) % S::TY;
+            k = h / (2 * H * S::TY);
+            i = a < H ? a - H : S::TX + a - H;
+        } else if (h < S::HX + S::HY) {
+            const int r = h - S::HX;
+            i = r % S::TX;
+            a = (r / S::TX) % (2 * H);
+            k = r / (S::TX * 2 * H);
+            j = a < H ? a - H : S::TY + a - H;
+        } else {
+            const int r = h - S::HX - S::HY;
+            i = r % S::TX;
+            j = (r / S::TX) % S::TY;
+            a = r / (S::TX * S::TY);
+            k = a < H ? a - H : S::TZ + a - H;
+        }
+        stage(i, j, k);
     }
-    uint16_t f[16];
-    features<double>(al, rh, pr, sqrt_eps, f);
-    uint4 *xo = (uint4 *)(X + t * 16);
-    const uint32_t *f32 = (const uint32_t *)f;
-    xo[0] = make_uint4(f32[0], f32[1], f32[2], f32[3]);
-    xo[1] = make_uint4(f32[4], f32[5], f32[6], f32[7]);
-    double dev = 0.0;
+    __syncthreads();
+    const int x = x0 + tx, y = y0 + ty, z = z0 + tz;
+    if (x >= g.n[0] || y >= g.n[1] || z >= g.n[2]) return;
+    const int64_t c = ((int64_t)z * g.n[1] + y) * g.n[0] + x;
+    const int p = ((tz + S::OZ) * S::PY + ty + S::OY) * S::PX + tx + H;
+#pragma unroll 1
+    for (int d = 0; d < NDIM; d++) {
+        const int64_t t = d * cells + c;
+        const int s = d == 0 ? 1 : (d == 1 ? S::PX : S::PX * S::PY), p0 = p - 2 * s;
+        // Differences to the centre.  The pressure's are taken before the
+        // rounding of the neighbour's product (one FMA), except the one next
+        // above the centre: where pressures differ by rounding alone these
+        // set the features' bits, and samples keep their bits.  The weights
+        // are those of the rounded values.
+        double dif[3][5], pr[5];
+        const double a2 = s_w[A][p], r2 = s_w[0][p] + s_w[1][p];
+        double pr2 = s_w[E][p] * s_ig[p];
+        __asm__("" : "+v"(pr2));   // rounded
 #pragma unroll
-    for (int v = 0; v < NV; v++) {
-        const double s[5] = {w[0][v], w[1][v], w[2][v], w[3][v], w[4][v]};
-        dev = fmax(dev, weno_deviation(s, g.eps));
+        for (int j = 0; j < 5; j++) {
+            const int o = p0 + j * s;
+            dif[0][j] = s_w[A][o] - a2;
+            dif[1][j] = (s_w[0][o] + s_w[1][o]) - r2;
+            pr[j] = s_w[E][o] * s_ig[o];
+            __asm__("" : "+v"(pr[j]));   // rounded
+            dif[2][j] = j == 3 ? pr[j] - pr2 : __builtin_fma(s_w[E][o], s_ig[o], -pr2);
+        }
+        uint16_t f[16];
+        features_of<double>(dif, sqrt_eps, f);
+        uint4 *xo = (uint4 *)(X + t * 16);
+        const uint32_t *f32 = (const uint32_t *)f;
+        xo[0] = make_uint4(f32[0], f32[1], f32[2], f32[3]);
+        xo[1] = make_uint4(f32[4], f32[5], f32[6], f32[7]);
+        double dev = 0.0;
+#pragma unroll
+        for (int v = 0; v < NV; v++) dev = fmax(dev, v == E ? weno_deviation(pr, 1, g.eps) : weno_deviation(&s_w[v][p0], s, g.eps));
+        Y[t] = dev < threshold ? 1 : 0;
+        if (D) D[t] = dev;
     }
-    Y[t] = dev < threshold ? 1 : 0;
-    if (D) D[t] = dev;
 }
 
 __global__ void __launch_bounds__(kThreads)
@@ -356,15 +416,18 @@ int mfc_harvest(mfc_grid *h, void *q, uint16_t *features, uint8_t *labels, doubl
     int st = mfc_fill_ghosts(h, q, stream);
     if (st) return st;
     hipStream_t s = (hipStream_t)stream;
-    const int64_t n = h->cells * h->g.ndim;
-    const unsigned blocks = (unsigned)((n + kThreads - 1) / kThreads);
-    const double se = std::sqrt(h->g.eps);
-    const double *qd = (const double *)q;
-    switch (h->g.ndim) {
-    case 1: hipLaunchKernelGGL(k_harvest<1>, dim3(blocks), dim3(kThreads), 0, s, h->g, qd, features, labels, maxdev, se, 0.01, h->cells); break;
-    case 2: hipLaunchKernelGGL(k_harvest<2>, dim3(blocks), dim3(kThreads), 0, s, h->g, qd, features, labels, maxdev, se, 0.01, h->cells); break;
-    default: hipLaunchKernelGGL(k_harvest<3>, dim3(blocks), dim3(kThreads), 0, s, h->g, qd, features, labels, maxdev, se, 0.01, h->cells); break;
-    }
+    const double se = std::sqrt(h->g.eps), *qd = (const double *)q;
+    auto launch = [&](auto nd) {
+        using S = HarvestTile<decltype(nd)::value>;
+        const Grid &g = h->g;
+        const int64_t tiles = (int64_t)((g.n[0] + S::TX - 1) / S::TX) * ((g.n[1] + S::TY - 1) / S::TY) *
+                              ((g.n[2] + S::TZ - 1) / S::TZ);
+        hipLaunchKernelGGL(k_harvest<decltype(nd)::value>, dim3((unsigned)tiles), dim3(kThreads), 0, s, g, qd, features, labels, maxdev,
+                           se, 0.01, h->cells);
+    };
+    if (h->g.ndim == 1) launch(std::integral_constant<int, 1>{});
+    else if (h->g.ndim == 2) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 3>{});
     return hip_status(hipGetLastError(), "harvest launch");
 }
 

@@ -42,23 +42,54 @@ typedef short s4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-// float -> bf16 bits, nearest with ties to even (finite inputs)
+// float -> bf16 bits, nearest with ties to even (the gfx950 conversion)
 __device__ __forceinline__ uint16_t bf16_bits(float x)
 {
-    uint32_t u = __float_as_uint(x);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    return __builtin_bit_cast(uint16_t, (__bf16)x);
 }
 
-// double -> bf16 bits, rounded once from the double: round the significand
-// to 8 bits in the double's own encoding, after which the conversion to
-// float and the truncation to 16 bits are exact.
+// double -> bf16 bits, rounded once from the double: the significand is cut
+// to the 20 bits of the double's high word with every bit below or-ed into
+// the last (round to odd), after which the conversion to float is exact and
+// the rounding to bf16 is that of the double.
 __device__ __forceinline__ uint16_t bf16_bits(double x)
 {
-    uint64_t u = (uint64_t)__double_as_longlong(x);
-    u += ((1ull << 44) - 1) + ((u >> 45) & 1ull);
-    u &= ~((1ull << 45) - 1);
-    return (uint16_t)(__float_as_uint((float)__longlong_as_double((long long)u)) >> 16);
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32) | (lo < 1u ? lo : 1u);
+    float f = (float)__longlong_as_double((long long)((uint64_t)hi << 32));
+    __asm__("" : "+v"(f));   // the two conversions are not to be taken for one from double (ten instructions)
+    return bf16_bits(f);
+}
+
+// Divisor of several quotients: the reciprocal refined until it is correctly
+// rounded, then per quotient a product and one correction with the exact
+// remainder, which gives the correctly rounded quotient (Markstein; finite
+// operands whose quotient and remainder are normal): three instructions per
+// quotient where a division takes ten and a reciprocal of its own.  With the
+// one-instruction rounding to bf16 the routed 112^3 FP32 kernels went from
+// 182 + 120 us (x+y, z) to 160 + 104 us.
+template <class T>
+constexpr T kDivisorMax = sizeof(T) == 8 ? T(0x1p1000) : T(0x1p125f);   // below: a normal reciprocal
+__device__ __forceinline__ double divisor(double s)
+{
+    double r = __builtin_amdgcn_rcp(s);
+    r = __builtin_fma(__builtin_fma(-s, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-s, r, 1.0), r, r);
+}
+__device__ __forceinline__ float divisor(float s)
+{
+    const float r = __builtin_amdgcn_rcpf(s);
+    return __builtin_fmaf(__builtin_fmaf(-s, r, 1.0f), r, r);
+}
+__device__ __forceinline__ double quotient(double d, double s, double r)
+{
+    const double q = d * r;
+    return __builtin_fma(__builtin_fma(-q, s, d), r, q);
+}
+__device__ __forceinline__ float quotient(float d, float s, float r)
+{
+    const float q = d * r;
+    return __builtin_fmaf(__builtin_fmaf(-q, s, d), r, q);
 }
 
 __device__ __forceinline__ __bf16 as_bf16(uint16_t b) { return __builtin_bit_cast(__bf16, b); }
@@ -71,8 +102,10 @@ constexpr float kA = 0.044715f;
 
 __device__ __forceinline__ float tanh_f(float u)
 {
-    // 1 - 2 / (1 + e^(2u)); saturates to +-1 for large |u| (rcp(inf) = 0)
-    return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * u));
+    // 1 - 2 / (1 + e^(2u)); saturates to +-1 for large |u| (rcp(inf) = 0).
+    // e^(2u) = 2^(2 log2(e) u): twice the FP32 log2(e) is exact, so this is
+    // the rounding of log2(e) (2u) with one instruction less
+    return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(2.0f * 1.44269504f * u));
 }
 
 __device__ __forceinline__ float gelu(float x)
@@ -198,26 +231,44 @@ __device__ __forceinline__ float logit_tile(const Params &P, s4 xb, int lane)
     return z + P.b3;
 }
 
-// Features of one (cell, direction) from the three 5-cell stencils, as bf16
-// bits (16 values, the last 0).  sqrt_eps is sqrt(weno eps).
+__device__ __forceinline__ double maxabs(double m, double d) { return __builtin_fmax(m, __builtin_fabs(d)); }
+__device__ __forceinline__ float maxabs(float m, float d) { return __builtin_fmaxf(m, __builtin_fabsf(d)); }
+
+// Features of one (cell, direction) from the differences of its three 5-cell
+// stencils (alpha1, rho, p) to their centre values, as bf16 bits (16 values,
+// the last 0).  sqrt_eps is sqrt(weno eps).
 template <class T>
-__device__ __forceinline__ void features(const T *a, const T *r, const T *p, T sqrt_eps, uint16_t *out)
+__device__ __forceinline__ void features_of(const T (&d)[3][5], T sqrt_eps, uint16_t *out)
 {
-    const T *v3[3] = {a, r, p};
 #pragma unroll
     for (int m = 0; m < 3; m++) {
-        const T *v = v3[m];
-        T d[5], mx = T(0);
+        T mx = T(0);
 #pragma unroll
-        for (int j = 0; j < 5; j++) {
-            d[j] = v[j] - v[2];
-            mx = d[j] < T(0) ? (-d[j] > mx ? -d[j] : mx) : (d[j] > mx ? d[j] : mx);
-        }
+        for (int j = 0; j < 5; j++) mx = maxabs(mx, d[m][j]);
         const T scale = mx > sqrt_eps ? mx : sqrt_eps;
+        if (scale < kDivisorMax<T>) {
+            const T r = divisor(scale);
 #pragma unroll
-        for (int j = 0; j < 5; j++) out[5 * m + j] = bf16_bits(d[j] / scale);
+            for (int j = 0; j < 5; j++) out[5 * m + j] = bf16_bits(quotient(d[m][j], scale, r));
+        } else {   // overflowed differences
+#pragma unroll
+            for (int j = 0; j < 5; j++) out[5 * m + j] = bf16_bits(d[m][j] / scale);
+        }
     }
     out[15] = 0;
+}
+
+// The same from the stencil values.
+template <class T>
+__device__ __forceinline__ void features(const T *a, const T *rho, const T *p, T sqrt_eps, uint16_t *out)
+{
+    const T *v[3] = {a, rho, p};
+    T d[3][5];
+#pragma unroll
+    for (int m = 0; m < 3; m++)
+#pragma unroll
+        for (int j = 0; j < 5; j++) d[m][j] = v[m][j] - v[m][2];
+    features_of<T>(d, sqrt_eps, out);
 }
 
 // Wavefront-cooperative decision: every lane supplies the features of its

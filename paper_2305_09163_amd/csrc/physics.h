@@ -171,8 +171,10 @@ __device__ __forceinline__ bool nonphysical(T rho, T c2)
 // Conservative -> primitive for one cell; returns true if non-physical
 // (rho <= 0, c^2 <= 0 or non-finite).  For float storage the pressure is
 // recovered in FP64 from the stored (float) energy, momenta and fractions.
+// pf non-null: receives the two factors of the FP64 pressure, whose product is
+// p before its rounding.
 template <int NDIM, class T>
-__device__ __forceinline__ bool cons_to_prim(const Grid &g, const T *q, T *w)
+__device__ __forceinline__ bool cons_to_prim(const Grid &g, const T *q, T *w, double *pf = nullptr)
 {
     constexpr int E = 2 + NDIM, A = 3 + NDIM;
     const T rho = q[0] + q[1];
@@ -190,7 +192,11 @@ __device__ __forceinline__ bool cons_to_prim(const Grid &g, const T *q, T *w)
     // the FP32 form stores p as float: the hardware estimate of 1/Gamma
     // (about 24 correct bits) is as accurate as that rounding
     const double iG = std::is_same<T, float>::value ? __builtin_amdgcn_rcp(Gam) : rcp(Gam);
-    const double p = (double(q[E]) - 0.5 * ke - Pi) * iG;
+    const double pn = double(q[E]) - 0.5 * ke - Pi, p = pn * iG;
+    if (pf) {
+        pf[0] = pn;
+        pf[1] = iG;
+    }
     w[E] = T(p);
     // c^2 = ((Gamma + 1) p + Pi) / (Gamma rho): its sign and finiteness
     // without the division
