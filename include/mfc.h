@@ -334,8 +334,9 @@ int mfc_trainer_infer(mfc_trainer *t, const uint16_t *features, int64_t n, float
 typedef struct mfc_batch mfc_batch;
 
 /* Launch configuration of the batched right-hand-side kernel:
- *   shape  tile of one work item: 0 = 16 x 16, 1 = 32 x 8, 2 = 64 x 4 cells;
- *   groups persistent workgroups per compute unit: 0 = 1, 1 = 2, 2 = 4;
+ *   shape  tile of one work item: 0 = 16 x 14, 1 = 32 x 6, 2 = 24 x 8 cells;
+ *   groups persistent workgroups per compute unit: 0 = 1, 1 = 2, 2 = 4 (no
+ *          more than its LDS holds: FP64 two);
  *   xcd    1 = give each XCD a contiguous range of work items (neighbouring
  *          tiles share one L2), 0 = deal items round-robin. */
 typedef struct {

@@ -9,7 +9,7 @@
 //   k_batch_stage      the right-hand side of eq. (fvmdis) (Sec. 3.1-3.2.1)
 //                      and the stage combination; a persistent kernel: a
 //                      fixed set of workgroups walks the flat list of
-//                      (run, tile) work items, 16 x 16 (or autotuned) tiles
+//                      (run, tile) work items, 16 x 14 (or autotuned) tiles
 //                      of the LDS-staged x/y sweep.  It reads neighbours
 //                      past a domain face through the boundary rule
 //                      (bc_cell: the values a ghost fill would write, bit
@@ -24,14 +24,14 @@
 #include <map>
 #include <new>
 
-#include "charbc.h"
-#include "internal.h"
+#include "tile2.h"
 
 namespace mfc {
 namespace {
 
 constexpr int kBT = 256;          // threads per workgroup
-constexpr int kWsBlocks = 8;      // wave-speed workgroups per run
+// wave-speed workgroups per run (64 runs of 64 .. 512 cells a side in FP32: 36 us; with 8, 102)
+constexpr int kWsBlocks = 64;
 constexpr int kXcds = 8;          // accelerator complex dies of the MI355X
 
 template <class T>
@@ -39,7 +39,6 @@ struct RunDev {
     Grid g;
     T *q;          // caller's state (step input and output)
     T *a, *b;      // stage registers q^(1), q^(2)
-    int tiles_x;   // for the stage kernel's tile decode (set per tile shape)
 };
 
 // ------------------------------------------------------------ wave speed
@@ -66,7 +65,7 @@ __global__ void __launch_bounds__(kBT) k_batch_wavespeed(const RunDev<T> *__rest
         const double cs = sqrtT(sound2<double>(Gam, Pi, double(wc[0]) + double(wc[1]), double(wc[4])));
         smax = __builtin_fmax(smax, __builtin_fmax(__builtin_fabs(double(wc[2])), __builtin_fabs(double(wc[3]))) + cs);
     }
-    if (bad) atomicOr(flag, 2);
+    if (bad) raise_flag(flag, 2);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) smax = __builtin_fmax(smax, __shfl_xor(smax, o, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = smax;
@@ -78,24 +77,30 @@ __global__ void __launch_bounds__(kBT) k_batch_wavespeed(const RunDev<T> *__rest
     }
 }
 
-// Per-run step size and accumulated time: scal[3 r + 0..2] = smax, dt, t.
-// The maximum comes from the wave-speed partials, or (carried) from the
-// maxima the previous step's last stage accumulated in cmax, kept as the
-// bit patterns of non-negative doubles (which order as integers); either
-// way cmax is cleared for the next accumulation.
-__global__ void k_batch_dt(const double *__restrict__ partial, unsigned long long *__restrict__ cmax,
-                           double *__restrict__ scal, const double *__restrict__ dxmin, int nrun, double cfl,
-                           int carried)
+// Per-run step size and accumulated time: scal[3 r + 0..2] = smax, dt, t, one
+// workgroup per run.  The maximum comes from run r's wave-speed partials, or
+// (carried) from those that the previous step's last stage left for its items,
+// first[r] .. first[r + 1] - 1, kItemSpeeds per item.
+constexpr int kItemSpeeds = 4;
+__global__ void __launch_bounds__(kBT) k_batch_dt(const double *__restrict__ partial, const double *__restrict__ carried,
+                                                  const int *__restrict__ first, double *__restrict__ scal,
+                                                  const double *__restrict__ dxmin, double cfl)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nrun) return;
+    __shared__ double red[kBT / 64];
+    const int r = blockIdx.x;
     double m = 0.0;
     if (carried) {
-        m = __longlong_as_double((long long)cmax[r]);
-    } else {
-        for (int b = 0; b < kWsBlocks; b++) m = __builtin_fmax(m, partial[r * kWsBlocks + b]);
+        const int end = kItemSpeeds * first[r + 1];
+#pragma unroll 8
+        for (int b = kItemSpeeds * first[r] + threadIdx.x; b < end; b += kBT) m = __builtin_fmax(m, carried[b]);
+    } else if (threadIdx.x < kWsBlocks) {
+        m = partial[r * kWsBlocks + threadIdx.x];
     }
-    cmax[r] = 0ull;
+    m = wave_max(m);
+    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = m;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < kBT / 64; w++) m = __builtin_fmax(m, red[w]);
     const double dt = cfl * dxmin[r] / m;
     scal[3 * r + 0] = m;
     scal[3 * r + 1] = dt;
@@ -103,68 +108,24 @@ __global__ void k_batch_dt(const double *__restrict__ partial, unsigned long lon
 }
 
 // ------------------------------------------------------------------ stage
-// One (run, tile) work item: the 2D right-hand side of a TX x TY tile and its
-// stage combination, with the plane and the face values staged in LDS.
-template <int TX, int TY, class T>
-struct Tile2 {
-    static constexpr int NV = 6, PX = TX + 2 * NG, PY = TY + 2 * NG;
-    static constexpr int NPX = (TX + 2) * TY, NFX = (TX + 1) * TY;
-    static constexpr int NPY = TX * (TY + 2), NFY = TX * (TY + 1);
-    static constexpr int NP = NPX > NPY ? NPX : NPY, NF = NFX > NFY ? NFX : NFY;
-    static constexpr int NHALO = 2 * NG * (TX + TY);
-};
-
+// One (run, tile) work item after the other (a tile is its column and, in the
+// upper 16 bits, its row), each the tile of tile2.h; the
+// cells of the next item are loaded while the current one is worked on.
+// Wavefronts per SIMD: two workgroups per CU in FP64 (74 KB of LDS each), four
+// in FP32 (64 registers; three at 72 registers take 1.5 % longer).  CHAR: a run of the batch has characteristic faces.
 template <class T>
-__device__ __forceinline__ bool load6(const Grid &g, const T *__restrict__ q, int i, int j, T *w)
-{
-    const int64_t c = (int64_t)(j + NG) * g.stride[1] + (i + NG);
-    T qc[6];
-#pragma unroll
-    for (int v = 0; v < 6; v++) qc[v] = q[v * g.vstride + c];
-    const bool bad = cons_to_prim<2, T>(g, qc, w);
-    const int outside = (i < 0 || i >= g.n[0]) + (j < 0 || j >= g.n[1]);
-    return bad && outside <= 1;
-}
+constexpr int kStageWaves = sizeof(T) == 8 ? 4 : 8;
 
-// Characteristic rates (charbc.h, Sec. 3.3) of the boundary cell at tile
-// position (r, c) on face SIDE of dimension D, from the cell and the next
-// two cells into the domain in the tile's LDS plane.
-template <int D, int SIDE, class T, int PY, int PX>
-__device__ __forceinline__ bool tile_char_rate(const Grid &g, const T (&pl)[6][PY][PX], int r, int c, T inv_dx,
-                                               T *rate)
-{
-    constexpr int sg = SIDE == 0 ? 1 : -1;
-    T W[3][6];
-#pragma unroll
-    for (int j = 0; j < 3; j++)
-#pragma unroll
-        for (int v = 0; v < 6; v++) W[j][v] = D == 0 ? pl[v][r][c + sg * j] : pl[v][r + sg * j][c];
-    return char_rate<2, D, SIDE, T>(g, W[0], W[1], W[2], inv_dx, one_sided<T>(g, D, SIDE), rate);
-}
-
-// LDS of a tile (plane, face-value pairs, fluxes): the FP64 64 x 4 tile
-// (88 KB) fits one workgroup per CU, every other shape at least two
-template <int TX, int TY, class T>
-constexpr int kBatchWaves =
-    sizeof(T) * (6 * Tile2<TX, TY, T>::PY * Tile2<TX, TY, T>::PX + 12 * Tile2<TX, TY, T>::NP + 7 * Tile2<TX, TY, T>::NF) >
-            80 * 1024 ? 1 : 2;
-
-template <int TX, int TY, class T>
-__global__ void __launch_bounds__(kBT, (kBatchWaves<TX, TY, T>))
+template <int TX, int TY, class T, bool CHAR>
+__global__ void __launch_bounds__((Tile2<TX, TY>::NT), (CHAR ? 4 : kStageWaves<T>))
     k_batch_stage(const RunDev<T> *__restrict__ runs, const int *__restrict__ item_run, const int *__restrict__ item_tile,
                   int nitems, const double *__restrict__ scal, int stage, int xcd, int *__restrict__ flag,
-                  unsigned long long *__restrict__ cmax)
+                  double *__restrict__ speeds)
 {
-    using S = Tile2<TX, TY, T>;
-    constexpr int NV = 6, A = 5, E = 4;
-    static_assert(TX * TY == kBT, "one cell per thread");
-    __shared__ T s_plane[NV][S::PY][S::PX];
-    __shared__ T s_pair[2 * NV][S::NP];
-    __shared__ T s_flux[NV + 1][S::NF];
-    const int tid = threadIdx.x, tx = tid % TX, ty = tid / TX;
-    const T ca = T(stage == 1 ? 0.0 : (stage == 2 ? 0.75 : 1.0 / 3.0));
-    const T cb = T(stage == 1 ? 1.0 : (stage == 2 ? 0.25 : 2.0 / 3.0));
-    bool bad = false;
+    using S = Tile2<TX, TY>;
+    __shared__ Tile2Lds<T, S> L;
+    const Role2<S> R;
+    bool bad = false, read = false, next_read = false;
 
     // Work items: round-robin over the workgroups, or (xcd != 0) contiguous
     // runs of items per XCD, so that neighbouring tiles, which read each
@@ -177,180 +138,36 @@ __global__ void __launch_bounds__(kBT, (kBatchWaves<TX, TY, T>))
         it1 = (int)((int64_t)(x + 1) * nitems / kXcds);
         istep = per;
     }
+    T qc[6], qn[6];
+    auto load = [&](int it, T *to) {
+        const int tile = item_tile[it], x0 = (tile & 0xffff) * TX, y0 = (tile >> 16) * TY;
+        const RunDev<T> &D = runs[item_run[it]];
+        const T *q = stage == 1 ? D.q : (stage == 2 ? D.a : D.b);
+        return R.loads ? load_cell2<T>(D.g, q, x0 + R.lx, y0 + R.ly, true, inner2<S>(D.g, x0, y0), to) : false;
+    };
+    if (it0 < it1) next_read = load(it0, qn);
     for (int it = it0; it < it1; it += istep) {
         const int run = item_run[it], tile = item_tile[it];
-        const RunDev<T> &R = runs[run];
-        const Grid &g = R.g;
-        const T *q = stage == 1 ? R.q : (stage == 2 ? R.a : R.b);
-        T *out = stage == 1 ? R.a : (stage == 2 ? R.b : R.q);
-        const T *q0 = R.q;
-        const T hdt = T(scal[3 * run + 1]);
-        const T eps = T(g.eps), idx = T(g.inv_dx[0]), idy = T(g.inv_dx[1]);
-        const int x0 = (tile % R.tiles_x) * TX, y0 = (tile / R.tiles_x) * TY;
-        const int xmax = g.n[0] + NG - 1, ymax = g.n[1] + NG - 1;
-        const int gx = x0 + tx, gy = y0 + ty;
-        const bool own = gx < g.n[0] && gy < g.n[1];
-        // cell (i, j) of the tile's window through the boundary rule (cells
-        // past a ragged tile edge load a duplicate whose results are dropped)
-        auto bx = [&](int i) { return bc_cell(min(i, xmax), g.n[0], g.bc[0], g.bc[1]); };
-        auto by = [&](int j) { return bc_cell(min(j, ymax), g.n[1], g.bc[2], g.bc[3]); };
-        T wk[NV];
-        bad |= load6<T>(g, q, bx(gx), by(gy), wk);
+        const RunDev<T> &D = runs[run];
+        const T *q = stage == 1 ? D.q : (stage == 2 ? D.a : D.b);
+        T *out = stage == 1 ? D.a : (stage == 2 ? D.b : D.q);
 #pragma unroll
-        for (int v = 0; v < NV; v++) s_plane[v][ty + NG][tx + NG] = wk[v];
-        for (int h = tid; h < S::NHALO; h += kBT) {
-            int li, lj;
-            if (h < 2 * NG * TY) {
-                const int c = h % (2 * NG), row = h / (2 * NG);
-                li = c < NG ? c : TX + c;
-                lj = row + NG;
-            } else {
-                const int h2 = h - 2 * NG * TY;
-                const int c = h2 % TX, r = h2 / TX;
-                li = c + NG;
-                lj = r < NG ? r : TY + r;
-            }
-            T w[NV];
-            bad |= load6<T>(g, q, bx(x0 + li - NG), by(y0 + lj - NG), w);
-#pragma unroll
-            for (int v = 0; v < NV; v++) s_plane[v][lj][li] = w[v];
+        for (int v = 0; v < 6; v++) qc[v] = qn[v];
+        read = next_read;
+        const double sp = tile2_stage<T, S, false, 5, false, CHAR>(
+            D.g, L, R, (tile & 0xffff) * TX, (tile >> 16) * TY, qc, read, q, D.q, out, stage, speeds != nullptr,
+            bad, nullptr, nullptr, 0.f, T(0),
+            [&] {
+                if (it + istep < it1) next_read = load(it + istep, qn);
+            },
+            [&] { return scal[3 * run + 1]; });
+        if (speeds && R.sweep == 0) {
+            static_assert(S::NS / 64 == kItemSpeeds, "one maximum per wavefront of cells");
+            const double m = wave_max(sp);
+            if (threadIdx.x % 64 == 0) speeds[kItemSpeeds * it + threadIdx.x / 64] = m;
         }
-        __syncthreads();
-        for (int p = tid; p < S::NPX; p += kBT) {
-            const int row = p / (TX + 2), c = p % (TX + 2);
-#pragma unroll
-            for (int v = 0; v < NV; v++) {
-                const T *s = &s_plane[v][row + NG][c];
-                weno5_pair(s[0], s[1], s[2], s[3], s[4], eps, s_pair[v][p], s_pair[NV + v][p]);
-            }
-        }
-        __syncthreads();
-        for (int f = tid; f < S::NFX; f += kBT) {
-            const int row = f / (TX + 1), fi = f % (TX + 1);
-            const int pl = row * (TX + 2) + fi;
-            T wL[NV], wR[NV], F[NV], uf;
-#pragma unroll
-            for (int v = 0; v < NV; v++) {
-                wL[v] = s_pair[v][pl];
-                wR[v] = s_pair[NV + v][pl + 1];
-            }
-            const bool b = hllc<2, 0, T>(g, wL, wR, F, uf);
-            bad |= b && (y0 + row < g.n[1]) && (x0 + fi <= g.n[0]);
-#pragma unroll
-            for (int v = 0; v < NV; v++) s_flux[v][f] = F[v];
-            s_flux[NV][f] = uf;
-        }
-        __syncthreads();
-        T L[NV], divu;
-        {
-            const int f = ty * (TX + 1) + tx;
-#pragma unroll
-            for (int v = 0; v < NV; v++) L[v] = (s_flux[v][f] - s_flux[v][f + 1]) * idx;
-            divu = (s_flux[NV][f + 1] - s_flux[NV][f]) * idx;
-        }
-        // Characteristic faces (Sec. 3.3): the boundary cell of such a face
-        // takes the characteristic rates in place of its terms normal to it.
-        // The rates of x faces are taken here, while s_plane is this item's
-        // for every thread, and put in place of the x terms after the y
-        // sweep; every other cell sums its terms exactly as the single-grid
-        // kernel does.
-        const int xside = !own ? -1
-                               : (gx == 0 && g.bc[0] == MFC_BC_CHARACTERISTIC)
-                                     ? 0
-                                     : ((gx == g.n[0] - 1 && g.bc[1] == MFC_BC_CHARACTERISTIC) ? 1 : -1);
-        const int yside = !own ? -1
-                               : (gy == 0 && g.bc[2] == MFC_BC_CHARACTERISTIC)
-                                     ? 0
-                                     : ((gy == g.n[1] - 1 && g.bc[3] == MFC_BC_CHARACTERISTIC) ? 1 : -1);
-        T xrate[NV];
-        if (xside == 0) bad |= tile_char_rate<0, 0>(g, s_plane, ty + NG, tx + NG, idx, xrate);
-        else if (xside == 1) bad |= tile_char_rate<0, 1>(g, s_plane, ty + NG, tx + NG, idx, xrate);
-        for (int p = tid; p < S::NPY; p += kBT) {
-            const int c = p % TX, r = p / TX;
-            const int li = c + NG;
-#pragma unroll
-            for (int v = 0; v < NV; v++)
-                weno5_pair(s_plane[v][r][li], s_plane[v][r + 1][li], s_plane[v][r + 2][li], s_plane[v][r + 3][li],
-                           s_plane[v][r + 4][li], eps, s_pair[v][p], s_pair[NV + v][p]);
-        }
-        __syncthreads();
-        for (int f = tid; f < S::NFY; f += kBT) {
-            const int c = f % TX, fr = f / TX;
-            const int pl = fr * TX + c;
-            T wL[NV], wR[NV], F[NV], uf;
-#pragma unroll
-            for (int v = 0; v < NV; v++) {
-                wL[v] = s_pair[v][pl];
-                wR[v] = s_pair[NV + v][pl + TX];
-            }
-            const bool b = hllc<2, 1, T>(g, wL, wR, F, uf);
-            bad |= b && (x0 + c < g.n[0]) && (y0 + fr <= g.n[1]);
-#pragma unroll
-            for (int v = 0; v < NV; v++) s_flux[v][f] = F[v];
-            s_flux[NV][f] = uf;
-        }
-        __syncthreads();
-        {
-            const int f = ty * TX + tx;
-#pragma unroll
-            for (int v = 0; v < NV; v++) L[v] += (s_flux[v][f] - s_flux[v][f + TX]) * idy;
-            divu += (s_flux[NV][f + TX] - s_flux[NV][f]) * idy;
-        }
-        if (xside >= 0 || yside >= 0) {   // boundary cells of characteristic faces
-            // the y terms again (the x ones: the sum minus them), each
-            // replaced by the face's rates where the cell is on such a face
-            // (s_plane stays this item's until the barrier at the end of it)
-            const int f = ty * TX + tx;
-            T yt[NV], rate[NV];
-#pragma unroll
-            for (int v = 0; v < NV; v++) yt[v] = (s_flux[v][f] - s_flux[v][f + TX]) * idy;
-            const T dy = (s_flux[NV][f + TX] - s_flux[NV][f]) * idy;
-            if (yside == 0) bad |= tile_char_rate<1, 0>(g, s_plane, ty + NG, tx + NG, idy, rate);
-            else if (yside == 1) bad |= tile_char_rate<1, 1>(g, s_plane, ty + NG, tx + NG, idy, rate);
-#pragma unroll
-            for (int v = 0; v < NV; v++) {
-                const T xs = xside >= 0 ? xrate[v] : L[v] - yt[v];
-                L[v] = xs + (yside >= 0 ? rate[v] : yt[v]);
-            }
-            divu = (xside >= 0 ? T(0) : divu - dy) + (yside >= 0 ? T(0) : dy);
-        }
-        L[A] += alpha_source<T>(g, wk[A], wk[E]) * divu;
-        double smax_item = 0.0;
-        if (own) {
-            const int64_t c = (int64_t)(gy + NG) * g.stride[1] + (gx + NG);
-            // every operand before the first store (out may alias q0)
-            T a0[NV], a1[NV];
-#pragma unroll
-            for (int v = 0; v < NV; v++) {
-                a0[v] = q0[v * g.vstride + c];
-                a1[v] = q[v * g.vstride + c];
-            }
-            T r[NV];
-#pragma unroll
-            for (int v = 0; v < NV; v++) {
-                r[v] = ca * a0[v] + cb * (a1[v] + hdt * L[v]);
-                out[v * g.vstride + c] = r[v];
-            }
-            if (cmax) {   // max_d |u_d| + c of the stored state, as k_batch_wavespeed forms it
-                T wr[NV];
-                cons_to_prim<2, T>(g, r, wr);
-                double Gam, Pi;
-                mixture<double>(g, double(wr[5]), Gam, Pi);
-                const double cs = sqrtT(sound2<double>(Gam, Pi, double(wr[0]) + double(wr[1]), double(wr[4])));
-                smax_item = __builtin_fmax(__builtin_fabs(double(wr[2])), __builtin_fabs(double(wr[3]))) + cs;
-            }
-        }
-        if (cmax) {   // wavefront maximum of the item, one atomic per wavefront
-            double m = smax_item;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) m = __builtin_fmax(m, __shfl_xor(m, o, 64));
-            if ((tid & 63) == 0) atomicMax(&cmax[run], (unsigned long long)__double_as_longlong(m));
-        }
-        // the next item overwrites s_plane only after every thread passed the
-        // barrier above; s_pair and s_flux after two more
-        __syncthreads();
     }
-    if (bad) atomicOr(flag, 1);
+    if (bad) raise_flag(flag, 1);
 }
 
 __global__ void k_batch_reset(double *scal, int n3, int *flag)
@@ -368,7 +185,7 @@ using namespace mfc;
 // Tile shapes the stage kernel is instantiated for, and workgroups per CU of
 // the persistent stage launch; the autotuner searches their product with the
 // XCD mapping on and off.
-static const int kShapes[][2] = {{16, 16}, {32, 8}, {64, 4}};
+static const int kShapes[][2] = {{16, 14}, {32, 6}, {24, 8}};
 constexpr int kNumShapes = 3;
 static const int kGroupsPerCu[] = {1, 2, 4};
 constexpr int kNumGroups = 3;
@@ -379,6 +196,7 @@ struct mfc_batch {
     int precision = MFC_FP32_MIXED;
     int device = 0;
     int cu_count = 0;
+    bool characteristic = false;   // a run has characteristic faces
     mfc_batch_tune tune{0, 1, 1};
     std::vector<mfc_grid_desc> desc;
     std::vector<Grid> grids;
@@ -388,12 +206,12 @@ struct mfc_batch {
     int *items[kNumShapes][2] = {};   // item_run, item_tile per shape (device)
     int nitems[kNumShapes] = {};
     double *partial = nullptr;        // [nrun * kWsBlocks]
-    unsigned long long *cmax = nullptr;  // [nrun] carried wave-speed maxima (bit patterns)
+    double *speeds = nullptr;         // [kItemSpeeds * items] carried wave-speed maxima
+    int *first[kNumShapes] = {};      // [nrun + 1] first item of a run, per shape (device)
     double *scal = nullptr;           // [3 * nrun]
     double *dxmin = nullptr;          // [nrun]
     int *flag = nullptr;
     std::vector<void *> bound_q;      // q pointers the device descriptors hold
-    int bound_shape = -1;
     hipGraphExec_t graph = nullptr;
     double graph_cfl = 0.0;
     int graph_steps = 0;
@@ -419,13 +237,11 @@ template <class T>
 int upload_runs(mfc_batch *b, void *const *q)
 {
     std::vector<RunDev<T>> h(b->nrun);
-    const int tx = kShapes[b->tune.shape][0];
     for (int r = 0; r < b->nrun; r++) {
         h[r].g = b->grids[r];
         h[r].q = (T *)q[r];
         h[r].a = (T *)b->stage[2 * r];
         h[r].b = (T *)b->stage[2 * r + 1];
-        h[r].tiles_x = (b->grids[r].n[0] + tx - 1) / tx;
     }
     // earlier steps may still read the descriptors
     hipError_t e = hipDeviceSynchronize();
@@ -435,7 +251,6 @@ int upload_runs(mfc_batch *b, void *const *q)
         return hip_status(e, "batch descriptor upload");
     }
     b->bound_q.assign(q, q + b->nrun);
-    b->bound_shape = b->tune.shape;
     return MFC_OK;
 }
 
@@ -443,7 +258,7 @@ int bind(mfc_batch *b, void *const *q)
 {
     for (int r = 0; r < b->nrun; r++)
         if (!q[r]) return fail(MFC_E_ARG, "null state pointer in the batch");
-    bool same = b->bound_q.size() == (size_t)b->nrun && b->bound_shape == b->tune.shape;
+    bool same = b->bound_q.size() == (size_t)b->nrun;
     for (int r = 0; same && r < b->nrun; r++) same = b->bound_q[r] == q[r];
     if (same) return MFC_OK;
     drop_graph(b);
@@ -452,27 +267,35 @@ int bind(mfc_batch *b, void *const *q)
 
 unsigned stage_groups(const mfc_batch *b)
 {
-    const int64_t want = (int64_t)kGroupsPerCu[b->tune.groups] * b->cu_count;
+    // no more than are resident at once: the items are dealt in advance
+    const int fit = b->characteristic || b->precision == MFC_FP64 ? 2 : 4;
+    const int64_t want = (int64_t)std::min(kGroupsPerCu[b->tune.groups], fit) * b->cu_count;
     const int64_t n = std::min<int64_t>(want, b->nitems[b->tune.shape]);
     return (unsigned)((n + kXcds - 1) / kXcds * kXcds);
 }
 
 template <class T>
-void launch_stage(mfc_batch *b, int st, hipStream_t s, unsigned long long *cmax = nullptr)
+void launch_stage(mfc_batch *b, int st, hipStream_t s, double *speeds = nullptr)
 {
     const RunDev<T> *runs = (const RunDev<T> *)b->runs;
     const int sh = b->tune.shape, nitems = b->nitems[sh], xcd = b->tune.xcd;
     const int *ir = b->items[sh][0], *it = b->items[sh][1];
-    const dim3 grid(stage_groups(b)), block(kBT);
+    const dim3 grid(stage_groups(b)), block(Tile2<16, 14>::NT);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (b->timing && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess)
         (void)hipEventRecord(e0, s);
-    if (sh == 0)
-        hipLaunchKernelGGL((k_batch_stage<16, 16, T>), grid, block, 0, s, runs, ir, it, nitems, b->scal, st, xcd, b->flag, cmax);
-    else if (sh == 1)
-        hipLaunchKernelGGL((k_batch_stage<32, 8, T>), grid, block, 0, s, runs, ir, it, nitems, b->scal, st, xcd, b->flag, cmax);
-    else
-        hipLaunchKernelGGL((k_batch_stage<64, 4, T>), grid, block, 0, s, runs, ir, it, nitems, b->scal, st, xcd, b->flag, cmax);
+    auto launch = [&](auto tx, auto ty) {
+        constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value;
+        if (b->characteristic)
+            hipLaunchKernelGGL((k_batch_stage<TX, TY, T, true>), grid, block, 0, s, runs, ir, it, nitems, b->scal, st, xcd,
+                               b->flag, speeds);
+        else
+            hipLaunchKernelGGL((k_batch_stage<TX, TY, T, false>), grid, block, 0, s, runs, ir, it, nitems, b->scal, st,
+                               xcd, b->flag, speeds);
+    };
+    if (sh == 0) launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 14>{});
+    else if (sh == 1) launch(std::integral_constant<int, 32>{}, std::integral_constant<int, 6>{});
+    else launch(std::integral_constant<int, 24>{}, std::integral_constant<int, 8>{});
     if (e1) {
         (void)hipEventRecord(e1, s);
         b->ev.emplace_back(e0, e1);
@@ -482,8 +305,8 @@ void launch_stage(mfc_batch *b, int st, hipStream_t s, unsigned long long *cmax 
 }
 
 // One step of every run.  carried_in: the per-run maxima of this step's
-// input were accumulated in cmax by the previous step's last stage;
-// carry_out: have this step's last stage accumulate those of its output.
+// input were left in speeds by the previous step's last stage;
+// carry_out: have this step's last stage leave those of its output.
 template <class T>
 int enqueue_step(mfc_batch *b, double cfl, hipStream_t s, bool carried_in, bool carry_out)
 {
@@ -491,11 +314,11 @@ int enqueue_step(mfc_batch *b, double cfl, hipStream_t s, bool carried_in, bool 
     if (!carried_in)
         hipLaunchKernelGGL((k_batch_wavespeed<T>), dim3(b->nrun * kWsBlocks), dim3(kBT), 0, s, runs, b->partial,
                            b->flag);
-    hipLaunchKernelGGL(k_batch_dt, dim3((b->nrun + 63) / 64), dim3(64), 0, s, b->partial, b->cmax, b->scal, b->dxmin,
-                       b->nrun, cfl, carried_in ? 1 : 0);
+    hipLaunchKernelGGL(k_batch_dt, dim3(b->nrun), dim3(kBT), 0, s, b->partial, carried_in ? b->speeds : nullptr,
+                       b->first[b->tune.shape], b->scal, b->dxmin, cfl);
     launch_stage<T>(b, 1, s);
     launch_stage<T>(b, 2, s);
-    launch_stage<T>(b, 3, s, carry_out ? b->cmax : nullptr);
+    launch_stage<T>(b, 3, s, carry_out ? b->speeds : nullptr);
     return hip_status(hipGetLastError(), "batch step launch");
 }
 
@@ -548,7 +371,9 @@ int mfc_batch_free(mfc_batch *b)
     for (int sh = 0; sh < kNumShapes; sh++)
         for (int k = 0; k < 2; k++)
             if (b->items[sh][k]) (void)hipFree(b->items[sh][k]);
-    for (void *p : {b->runs, (void *)b->cmax, (void *)b->partial, (void *)b->scal, (void *)b->dxmin, (void *)b->flag})
+    for (int *p : b->first)
+        if (p) (void)hipFree(p);
+    for (void *p : {b->runs, (void *)b->speeds, (void *)b->partial, (void *)b->scal, (void *)b->dxmin, (void *)b->flag})
         if (p) (void)hipFree(p);
     delete b;
     return MFC_OK;
@@ -607,6 +432,7 @@ int mfc_batch_init(const mfc_grid_desc *descs, int count, mfc_batch **out)
         g.p[2] = 1;
         g.off[0] = g.off[1] = NG;
         g.off[2] = 0;
+        for (int f = 0; f < 4; f++) b->characteristic |= d.bc[f] == MFC_BC_CHARACTERISTIC;
         for (int f = 0; f < 6; f++) g.bc[f] = f < 4 ? d.bc[f] : MFC_BC_EXTRAP;   // read by index (bc_cell)
         g.stride[0] = 1;
         g.stride[1] = g.p[0];
@@ -638,28 +464,31 @@ int mfc_batch_init(const mfc_grid_desc *descs, int count, mfc_batch **out)
     for (int r = 0; r < count; r++)
         for (int k = 0; k < 2; k++) alloc(&b->stage[2 * r + k], (size_t)6 * b->grids[r].vstride * elem(b));
     alloc(&b->runs, sizeof(RunDev<double>) * count);
-    alloc((void **)&b->cmax, sizeof(unsigned long long) * count);
     alloc((void **)&b->partial, sizeof(double) * count * kWsBlocks);
     alloc((void **)&b->scal, sizeof(double) * 3 * count);
     alloc((void **)&b->dxmin, sizeof(double) * count);
     alloc((void **)&b->flag, sizeof(int) * 2);
     for (int sh = 0; sh < kNumShapes && e == hipSuccess; sh++) {
-        std::vector<int> ir, it;
+        std::vector<int> ir, it, first;
         for (int r = 0; r < count; r++) {
+            first.push_back((int)ir.size());
             const int tx = (b->grids[r].n[0] + kShapes[sh][0] - 1) / kShapes[sh][0];
             const int ty = (b->grids[r].n[1] + kShapes[sh][1] - 1) / kShapes[sh][1];
             for (int t = 0; t < tx * ty; t++) {
                 ir.push_back(r);
-                it.push_back(t);
+                it.push_back(t % tx | t / tx << 16);
             }
         }
+        first.push_back((int)ir.size());
         b->nitems[sh] = (int)ir.size();
+        alloc((void **)&b->first[sh], sizeof(int) * first.size());
+        if (e == hipSuccess) e = hipMemcpy(b->first[sh], first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice);
         alloc((void **)&b->items[sh][0], sizeof(int) * ir.size());
         alloc((void **)&b->items[sh][1], sizeof(int) * it.size());
         if (e == hipSuccess) e = hipMemcpy(b->items[sh][0], ir.data(), sizeof(int) * ir.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(b->items[sh][1], it.data(), sizeof(int) * it.size(), hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess) e = hipMemset(b->cmax, 0, sizeof(unsigned long long) * count);   // set-up, not a graph node
+    alloc((void **)&b->speeds, sizeof(double) * kItemSpeeds * *std::max_element(b->nitems, b->nitems + kNumShapes));
     if (e == hipSuccess) e = hipMemcpy(b->dxmin, dxmin.data(), sizeof(double) * count, hipMemcpyHostToDevice);
     if (e == hipSuccess) {
         hipLaunchKernelGGL(k_batch_reset, dim3((3 * count + 255) / 256), dim3(256), 0, 0, b->scal, 3 * count, b->flag);

@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(kCbcThreads, MFC_CBC_WAVES)
         for (int o = 32; o > 0; o >>= 1) smax = __builtin_fmax(smax, __shfl_xor(smax, o, 64));
         if (threadIdx.x == 0) smax_partial[blockIdx.x] = smax;
     }
-    if (bad) atomicOr(flag, 1);
+    if (bad) raise_flag(flag, 1);
 }
 
 template <int NDIM, class T, int ORDER, bool STORED>

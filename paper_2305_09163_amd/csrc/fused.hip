@@ -15,7 +15,7 @@
 //     is computed once and shared by the two cells that own the face;
 //   - each thread then forms its cell's flux differences plus the
 //     alpha1 div(u) source and the SSP-RK3 stage combination.
-// 2D uses the same tile without the z march; 1D uses a 256-cell row.
+// 1D uses a 256-cell row; 2D has its own kernel (plane.hip).
 // With ROUTE = true every (cell, direction) is first classified by the learned
 // indicator of mlp.h (whole wavefronts at a time) and a smooth one takes the
 // linear fifth-order stencil for every variable instead of WENO5.
@@ -34,6 +34,7 @@ struct Shape {
     static constexpr int NT = TX * TY;
     static constexpr int NV = 4 + NDIM;
     static constexpr int PX = TX + 2 * NG;
+    static_assert(NDIM == 1 || NDIM == 3, "2D grids take plane.hip");
     static constexpr int PY = NDIM >= 2 ? TY + 2 * NG : 1;
     static constexpr int OY = NDIM >= 2 ? NG : 0;   // LDS row of the tile's first row
     static constexpr int NPX = (TX + 2) * TY;       // x reconstructions (cells -1 .. TX)
@@ -358,7 +359,7 @@ __global__ void __launch_bounds__(Shape<NDIM>::NT, 2)
             }
         }
     }
-    if (bad) atomicOr(flag, 1);
+    if (bad) raise_flag(flag, 1);
 }
 
 template <int NDIM, class T, bool ROUTE, int ORDER, bool STRETCH>
@@ -384,7 +385,6 @@ int rhs_fused_t(mfc_grid *h, const void *q, const void *q0, void *out, int mode,
     T *o = (T *)out;
     switch (h->g.ndim) {
     case 1: return rhs_fused<1, T, ROUTE, ORDER, STRETCH>(h, a, b, o, mode, dt, dt_dev, s);
-    case 2: return rhs_fused<2, T, ROUTE, ORDER, STRETCH>(h, a, b, o, mode, dt, dt_dev, s);
     default: return rhs_fused<3, T, ROUTE, ORDER, STRETCH>(h, a, b, o, mode, dt, dt_dev, s);
     }
 }

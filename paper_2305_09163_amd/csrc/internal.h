@@ -53,6 +53,63 @@ namespace mfc {
 constexpr int kReduceBlocks = 1024;
 constexpr int kReduceThreads = 256;
 
+// Raise a bit of a handle's non-physical flag.  The bit is looked at first:
+// once a run has left the physical states every wavefront raises it, and the
+// atomics of a launch all queue on the one word (253 x 181 cells: 9 us a
+// launch).
+#if defined(__HIPCC__)
+__device__ __forceinline__ void raise_flag(int *flag, int bit)
+{
+    if (!(*flag & bit)) atomicOr(flag, bit);
+}
+
+// Wavefront maximum, in every lane.
+__device__ __forceinline__ double wave_max(double m)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) m = __builtin_fmax(m, __shfl_xor(m, o, 64));
+    return m;
+}
+#endif
+
+// Step size of a stage whose kernel sets it itself (1D and 2D): in the first
+// stage of a step every workgroup reduces the wave-speed maxima that the
+// wave-speed kernel or the previous step's last stage left, which saves a
+// launch of its own where they are few; the later stages read the result.
+struct StepSize {
+    double cfl = 0.0, dt = 0.0, dxmin = 0.0;  // cfl > 0: cfl dxmin / speed, else dt
+    const double *speeds = nullptr;           // the maxima (the first stage of a CFL step)
+    int nspeeds = 0;
+    bool set = false;                         // the first stage sets the step size (else it is in scalars)
+    double *carry = nullptr;                  // non-null: a last stage writes the maxima of its result there
+    double *scalars = nullptr;                // the handle's: speed, step size, time
+    double *dt_out = nullptr;                 // the caller's word for the step size (a first stage)
+#if defined(__HIPCC__)
+    // This wavefront's maximum, to be gathered over the workgroup's wavefronts.
+    __device__ __forceinline__ double gather(int threads) const
+    {
+        double m = 0.0;
+        if (speeds)
+            for (int i = threadIdx.x; i < nspeeds; i += threads) m = __builtin_fmax(m, speeds[i]);
+        return wave_max(m);
+    }
+    // The step size from the gathered maximum; `one` is set in one thread of
+    // the launch.
+    __device__ __forceinline__ double finish(double m, bool one) const
+    {
+        if (!set) return scalars[1];
+        const double h = speeds ? cfl * dxmin / m : dt;
+        if (one) {
+            if (speeds) scalars[0] = m;
+            scalars[1] = h;
+            scalars[2] += h;
+            if (dt_out) *dt_out = h;
+        }
+        return h;
+    }
+#endif
+};
+
 // status helpers
 int fail(int status, const char *detail);
 int fail(int status, const std::string &detail);
@@ -93,6 +150,11 @@ int launch_rhs_staged(mfc_grid *h, const void *q, const void *q0, void *out, int
                       const double *dt_dev, hipStream_t s);
 int launch_rhs_fused(mfc_grid *h, const void *q, const void *q0, void *out, int mode, double dt,
                      const double *dt_dev, hipStream_t s);
+// 2D grids of the fused kernel (plane.hip): stages read past the faces through
+// the boundary rule, the bare right-hand side (mode 0) reads ghost cells.
+int launch_rhs_plane(mfc_grid *h, const void *q, const void *q0, void *out, int mode, const StepSize &ss, hipStream_t s);
+// Wave-speed maxima a carrying last stage leaves (one per wavefront of cells).
+int64_t plane_partials(const Grid &g);
 // Split path: cfl > 0 reduces the wave speeds of q in the x+y pass and sets
 // the step size before the z pass (the first stage of a CFL step); zmax
 // non-null (a last stage) has the z pass reduce the wave speeds of the state

@@ -196,7 +196,7 @@ __global__ void __launch_bounds__(kThreads) k_c2p(Grid g, const T *__restrict__ 
     T qc[NV], wc[NV];
 #pragma unroll
     for (int v = 0; v < NV; v++) qc[v] = q[v * g.vstride + c];
-    if (cons_to_prim<NDIM, T>(g, qc, wc)) atomicOr(flag, 1);
+    if (cons_to_prim<NDIM, T>(g, qc, wc)) raise_flag(flag, 1);
 #pragma unroll
     for (int v = 0; v < NV; v++) w[v * g.vstride + c] = wc[v];
 }
@@ -207,7 +207,8 @@ __global__ void __launch_bounds__(kThreads) k_c2p(Grid g, const T *__restrict__ 
 // through LDS.  Maxima are exact and order-independent.
 template <int NDIM, class T>
 __global__ void __launch_bounds__(kReduceThreads) k_wavespeed(Grid g, const T *__restrict__ q,
-                                                              double *__restrict__ partial, int *__restrict__ flag)
+                                                              double *__restrict__ partial,
+                                                              int *__restrict__ flag)
 {
     constexpr int NV = 4 + NDIM, E = 2 + NDIM, A = 3 + NDIM;
     __shared__ double red[kReduceThreads / 64];
@@ -240,7 +241,7 @@ __global__ void __launch_bounds__(kReduceThreads) k_wavespeed(Grid g, const T *_
             for (int d = 0; d < NDIM; d++) smax = __builtin_fmax(smax, __builtin_fabs(double(wc[2 + d])) + cs);
         }
     }
-    if (bad) atomicOr(flag, 2);
+    if (bad) raise_flag(flag, 2);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) smax = __builtin_fmax(smax, __shfl_xor(smax, o, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = smax;
@@ -383,6 +384,7 @@ int rhs_dispatch(mfc_grid *h, const void *q, const void *q0, void *out, int mode
     int st;
     if (h->desc.kernel == MFC_KERNEL_STAGED) st = launch_rhs_staged(h, q, q0, out, mode, dt, dt_dev, s);
     else if (h->desc.kernel == MFC_KERNEL_SPLIT) st = launch_rhs_split(h, q, q0, out, mode, dt, dt_dev, s, cfl, zmax);
+    else if (h->desc.ndim == 2) st = launch_rhs_plane(h, q, q0, out, mode, StepSize{}, s);   // mode 0
     else st = launch_rhs_fused(h, q, q0, out, mode, dt, dt_dev, s);
     // with characteristic faces, a wave-speed-reducing last stage leaves the
     // z faces' cells to the boundary pass, whose maxima follow the z kernel's
@@ -426,19 +428,19 @@ int fill_ghosts(mfc_grid *h, void *q, hipStream_t s)
 }
 
 template <class T>
-void wavespeed_t(mfc_grid *h, const T *q, hipStream_t s)
+void wavespeed_t(mfc_grid *h, const T *q, int blocks, hipStream_t s)
 {
     by_ndim(h->g.ndim, [&](auto nd) {
-        hipLaunchKernelGGL((k_wavespeed<decltype(nd)::value, T>), dim3(kReduceBlocks), dim3(kReduceThreads), 0, s,
-                           h->g, q, h->partial, h->flag);
+        hipLaunchKernelGGL((k_wavespeed<decltype(nd)::value, T>), dim3(blocks), dim3(kReduceThreads), 0, s, h->g, q,
+                           h->partial, h->flag);
         return 0;
     });
 }
 
-int wavespeed(mfc_grid *h, const void *q, hipStream_t s)
+int wavespeed(mfc_grid *h, const void *q, hipStream_t s, int blocks = kReduceBlocks)
 {
-    if (is_fp32(h)) wavespeed_t<float>(h, (const float *)q, s);
-    else wavespeed_t<double>(h, (const double *)q, s);
+    if (is_fp32(h)) wavespeed_t<float>(h, (const float *)q, blocks, s);
+    else wavespeed_t<double>(h, (const double *)q, blocks, s);
     return hip_status(hipGetLastError(), "wave-speed launch");
 }
 
@@ -547,7 +549,8 @@ int mfc_init_grid(const mfc_grid_desc *desc, mfc_grid **out)
     }
     h->partial_len = std::max<int64_t>(
         kReduceBlocks,
-        desc->ndim == 3 ? std::max(split_xy_blocks(g), split_z_partials(g) + cbc_stored_blocks(g)) : 0);
+        desc->ndim == 3 ? std::max(split_xy_blocks(g), split_z_partials(g) + cbc_stored_blocks(g))
+                        : (desc->ndim == 2 ? plane_partials(g) : 0));
     alloc((void **)&h->partial, h->partial_len * 8);
     alloc((void **)&h->scalars, 4 * 8);
     alloc((void **)&h->flag, 8);
@@ -669,9 +672,15 @@ namespace {
 // that stage's x+y pass forms its part of the combination.  With
 // characteristic faces the boundary pass, which changes the z faces' cells
 // after the z pass, reduces those cells itself.
+//
+// 2D grids of the fused kernel: so does the last stage's kernel; with
+// characteristic faces, whose boundary pass changes cells after it, every
+// step reduces its own.
+bool steps_by_tiles(const mfc_grid *h) { return h->desc.kernel == MFC_KERNEL_FUSED && h->desc.ndim == 2; }
+
 bool carries_wavespeed(const mfc_grid *h, double cfl)
 {
-    return cfl > 0.0 && h->desc.kernel == MFC_KERNEL_SPLIT;
+    return cfl > 0.0 && (h->desc.kernel == MFC_KERNEL_SPLIT || (steps_by_tiles(h) && !has_cbc(h)));
 }
 
 // Number of wave-speed maxima a carrying last stage leaves in h->partial.
@@ -680,18 +689,63 @@ int64_t carried_partials(const mfc_grid *h)
     return split_z_partials(h->g) + (has_cbc(h) ? cbc_stored_blocks(h->g) : 0);
 }
 
-// One SSP-RK3 step.  carried_in: the wave-speed partials of q^n are in
-// h->partial (written by the previous step's last stage); carry_out: have
-// this step's last stage write those of q^{n+1}.
+// One SSP-RK3 step.  carried_in: the wave-speed maxima of q^n are in
+// h->partial, written by the previous step's last stage; carry_out: have this
+// step's last stage write those of q^{n+1}; last: the last step of its call.
 int rk3_step_launches(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, bool carried_in, bool carry_out);
 
+// The same on a grid whose stage kernels read past the faces through the
+// boundary rule and set the step size themselves.  The ghost cells of q are
+// those a fill before every right-hand side leaves: of the last step's q^n.
+int rk3_step_tiles(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, bool carried_in, bool carry_out, bool last)
+{
+    // Up to this many maxima (four per tile) every workgroup of the first
+    // stage reduces them itself (253 x 181 cells, 832 maxima: within the
+    // launch's noise, against 5 us for a launch with its gap); more of them are
+    // reduced once by their own launch.
+    constexpr int kInStage = 2048;
+    int st;
+    void *A = h->stage_a, *B = h->stage_b;
+    if (last && (st = fill_ghosts(h, q, s))) return st;
+    StepSize first;
+    first.cfl = cfl;
+    first.dt = dt;
+    first.dxmin = h->g.dxmin;
+    first.scalars = h->scalars;
+    first.dt_out = h->dt_out;
+    first.set = true;
+    if (cfl > 0.0) {
+        const int blocks = (int)std::min<int64_t>(kReduceBlocks, blocks_for(h->cells));
+        if (!carried_in && (st = wavespeed(h, q, s, blocks))) return st;
+        first.nspeeds = carried_in ? (int)plane_partials(h->g) : blocks;
+        if (first.nspeeds > kInStage) {
+            launch_step_begin(h, h->partial, first.nspeeds, cfl, 0.0, s);
+            first.set = false;
+        } else {
+            first.speeds = h->partial;
+        }
+    }
+    const void *in[3] = {q, A, B};
+    void *out[3] = {A, B, q};
+    for (int mode = 1; mode <= 3; mode++) {
+        StepSize ss;
+        if (mode == 1) ss = first;
+        else ss.scalars = h->scalars;
+        if (carry_out && mode == 3) ss.carry = h->partial;
+        if ((st = launch_rhs_plane(h, in[mode - 1], q, out[mode - 1], mode, ss, s))) return st;
+        if (has_cbc(h) && (st = launch_cbc(h, in[mode - 1], out[mode - 1], mode, 0.0, h->scalars + 1, s))) return st;
+    }
+    return MFC_OK;
+}
+
 int rk3_step(mfc_grid *h, void *q, double cfl, double dt, double *dt_used_dev, hipStream_t s, bool carried_in,
-             bool carry_out)
+             bool carry_out, bool last)
 {
     // with a timing stride, only every stride-th step's launches are timed
     h->timing_skip = h->timing && (h->timing_step++ % h->timing_stride) != 0;
-    h->dt_out = dt_used_dev;   // written by the step's k_step_begin
-    const int st = rk3_step_launches(h, q, cfl, dt, s, carried_in, carry_out);
+    h->dt_out = dt_used_dev;   // written by the kernel that sets the step size
+    const int st = steps_by_tiles(h) ? rk3_step_tiles(h, q, cfl, dt, s, carried_in, carry_out, last)
+                                     : rk3_step_launches(h, q, cfl, dt, s, carried_in, carry_out);
     h->dt_out = nullptr;
     h->timing_skip = false;
     return st;
@@ -743,7 +797,7 @@ int mfc_rk3_step(mfc_grid *h, void *q, double cfl, double dt, double *dt_used_de
 {
     int st = check_step_args(h, q, cfl, dt);
     if (st) return st;
-    return rk3_step(h, q, cfl, dt, dt_used_dev, (hipStream_t)stream, false, false);
+    return rk3_step(h, q, cfl, dt, dt_used_dev, (hipStream_t)stream, false, false, true);
 }
 
 int mfc_run(mfc_grid *h, void *q, int nsteps, double cfl, double dt, void *stream)
@@ -754,7 +808,8 @@ int mfc_run(mfc_grid *h, void *q, int nsteps, double cfl, double dt, void *strea
     if (st) return st;
     const bool carry = carries_wavespeed(h, cfl);
     for (int n = 0; n < nsteps && st == MFC_OK; n++)
-        st = rk3_step(h, q, cfl, dt, nullptr, (hipStream_t)stream, carry && n > 0, carry && n + 1 < nsteps);
+        st = rk3_step(h, q, cfl, dt, nullptr, (hipStream_t)stream, carry && n > 0, carry && n + 1 < nsteps,
+                      n + 1 == nsteps);
     return st;
 }
 

@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(NT, (kXYWaves<T, ROUTE, STRETCH, KEEP>))
             smax_partial[((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = m;
         }
     }
-    if (bad) atomicOr(flag, 1);
+    if (bad) raise_flag(flag, 1);
 }
 
 // z direction + stage update.  Threads of a workgroup own 256 consecutive
@@ -812,7 +812,7 @@ __global__ void __launch_bounds__(kNZT, kZWaves<T>)
         if (lane == 0)
             smax_partial[((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * kZWavesWG + t / 64] = smax;
     }
-    if (bad) atomicOr(flag, 1);
+    if (bad) raise_flag(flag, 1);
 }
 
 dim3 xy_grid(const Grid &g)

@@ -48,7 +48,7 @@ class mfc_batch_tune(ctypes.Structure):
     _fields_ = [("shape", ctypes.c_int), ("groups", ctypes.c_int), ("xcd", ctypes.c_int)]
 
 
-BATCH_SHAPES = ((16, 16), (32, 8), (64, 4))
+BATCH_SHAPES = ((16, 14), (32, 6), (24, 8))
 BATCH_GROUPS_PER_CU = (1, 2, 4)
 
 _lib = None
