@@ -206,7 +206,8 @@ int mfc_max_wavespeed(mfc_grid *g, const void *q, double *smax_host, void *strea
  * (fvmdis) as in mfc_rhs), ghost fill
  * before every right-hand side (MFC_KERNEL_SPLIT applies the boundary
  * conditions by index instead, with the same result, and leaves the ghost
- * cells of q as they were).  If cfl > 0 the step size is
+ * cells of q as they were; MFC_KERNEL_FUSED in 1D and 2D applies them by
+ * index too and leaves in the ghost cells of q what a fill of q^n leaves).  If cfl > 0 the step size is
  * cfl * min_d dx_d / max_wavespeed(q^n), computed on the device with no host
  * synchronisation; otherwise dt (> 0) is used.  The step size taken and the
  * accumulated time are kept on the device (mfc_time); if dt_used_dev is not

@@ -150,6 +150,13 @@ int launch_rhs_staged(mfc_grid *h, const void *q, const void *q0, void *out, int
                       const double *dt_dev, hipStream_t s);
 int launch_rhs_fused(mfc_grid *h, const void *q, const void *q0, void *out, int mode, double dt,
                      const double *dt_dev, hipStream_t s);
+// 1D runs of the fused kernel (line.hip): whether nsteps steps take whole-step
+// launches, those steps, and the length of mfc_grid::partial they need.
+bool takes_line(const mfc_grid *h, int nsteps);
+int run_line(mfc_grid *h, void *q, int nsteps, double cfl, double dt, double *dt_out, hipStream_t s);
+int64_t line_partials(const Grid &g);
+// Wave speeds of q into kReduceBlocks partial maxima.
+int launch_wavespeed(mfc_grid *h, const void *q, hipStream_t s);
 // 2D grids of the fused kernel (plane.hip): stages read past the faces through
 // the boundary rule, the bare right-hand side (mode 0) reads ghost cells.
 int launch_rhs_plane(mfc_grid *h, const void *q, const void *q0, void *out, int mode, const StepSize &ss, hipStream_t s);

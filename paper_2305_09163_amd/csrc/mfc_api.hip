@@ -451,6 +451,8 @@ int64_t state_bytes(const mfc_grid *h) { return (int64_t)h->nvar * h->cells_padd
 
 int validate_desc(const mfc_grid_desc *d) { return validate(d); }
 
+int launch_wavespeed(mfc_grid *h, const void *q, hipStream_t s) { return wavespeed(h, q, s); }
+
 }  // namespace mfc
 
 using namespace mfc;
@@ -550,7 +552,7 @@ int mfc_init_grid(const mfc_grid_desc *desc, mfc_grid **out)
     h->partial_len = std::max<int64_t>(
         kReduceBlocks,
         desc->ndim == 3 ? std::max(split_xy_blocks(g), split_z_partials(g) + cbc_stored_blocks(g))
-                        : (desc->ndim == 2 ? plane_partials(g) : 0));
+                        : (desc->ndim == 2 ? plane_partials(g) : line_partials(g)));
     alloc((void **)&h->partial, h->partial_len * 8);
     alloc((void **)&h->scalars, 4 * 8);
     alloc((void **)&h->flag, 8);
@@ -797,6 +799,7 @@ int mfc_rk3_step(mfc_grid *h, void *q, double cfl, double dt, double *dt_used_de
 {
     int st = check_step_args(h, q, cfl, dt);
     if (st) return st;
+    if (takes_line(h, 1)) return run_line(h, q, 1, cfl, dt, dt_used_dev, (hipStream_t)stream);
     return rk3_step(h, q, cfl, dt, dt_used_dev, (hipStream_t)stream, false, false, true);
 }
 
@@ -806,6 +809,7 @@ int mfc_run(mfc_grid *h, void *q, int nsteps, double cfl, double dt, void *strea
     if (nsteps == 0) return MFC_OK;
     int st = check_step_args(h, q, cfl, dt);
     if (st) return st;
+    if (takes_line(h, nsteps)) return run_line(h, q, nsteps, cfl, dt, nullptr, (hipStream_t)stream);
     const bool carry = carries_wavespeed(h, cfl);
     for (int n = 0; n < nsteps && st == MFC_OK; n++)
         st = rk3_step(h, q, cfl, dt, nullptr, (hipStream_t)stream, carry && n > 0, carry && n + 1 < nsteps,
