@@ -63,7 +63,7 @@ struct Grid {
     // second-order one-sided derivative at the boundary cell's centre
     double cbc_cf[6][3];
 };
-constexpr int kStretchCoef = 42;
+constexpr int kStretchCoef = 30;
 
 // Store the normal finite-volume terms of a boundary cell of characteristic
 // face F (the split kernels; read back by the boundary post-pass).
@@ -363,58 +363,49 @@ __device__ __forceinline__ void recon_pair(T vm2, T vm1, T v0, T vp1, T vp2, T e
     }
 }
 
-// WENO5 on non-uniform cells from the 42 coefficients of the cell (layout in
-// stretch.hip): candidates, a1 and a2 of each stencil are linear in its
-// three values, beta_r = a1^2 + (13/3) a2^2, ideal weights per face.  FP64
-// directly, FP32 in the ratio form (weights relative to the smallest
-// (eps + beta)).  CF is the row in memory, or a copy of it in registers
-// (one load per cell for all its variables).
+// WENO5 on non-uniform cells from the cell's coefficient row (layout in
+// stretch.hip): a1, a2 and the candidates' increments over v0 of each stencil
+// are two products with its divided differences, beta_r = a1^2 + a2^2 (the
+// row's a2 carries sqrt(13/3)), ideal weights per face (the increments carry
+// theirs).  Through common denominators in FP64 and relative to the central
+// stencil in FP32, as weno5_pair: 59 instructions and one reciprocal per value
+// in FP64 (values instead of increments and a reciprocal per weight: 80 and
+// five).  CF is the row in memory, or a copy of it in registers (one load per
+// cell for all its variables).
 template <class T, class CF>
 __device__ __forceinline__ void weno5_nonuniform_pair(const CF &cf, T vm2, T vm1, T v0, T vp1, T vp2, T eps, T &plus,
                                                       T &minus)
 {
-    const T s[5] = {vm2, vm1, v0, vp1, vp2};
-    T pp[3], pm[3], e[3];
+    const T b = vm1 - vm2, a = v0 - vm1, c = vp1 - v0, d = vp2 - vp1;
+    const T lo[3] = {b, a, c}, hi[3] = {a, c, d};   // the differences of each stencil
+    T e[3], pp[3], pm[3];
 #pragma unroll
     for (int r = 0; r < 3; r++) {
-        T a1 = T(0), a2 = T(0);
-        pp[r] = pm[r] = T(0);
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-            pp[r] = fmaT(T(cf[3 * r + j]), s[r + j], pp[r]);
-            pm[r] = fmaT(T(cf[9 + 3 * r + j]), s[r + j], pm[r]);
-            a1 = fmaT(T(cf[18 + 3 * r + j]), s[r + j], a1);
-            a2 = fmaT(T(cf[27 + 3 * r + j]), s[r + j], a2);
-        }
-        e[r] = eps + fmaT(a1, a1, T(13.0 / 3.0) * a2 * a2);
+        const T a1 = fmaT(T(cf[2 * r]), lo[r], T(cf[2 * r + 1]) * hi[r]);
+        const T a2 = fmaT(T(cf[6 + 2 * r]), lo[r], T(cf[7 + 2 * r]) * hi[r]);
+        e[r] = fmaT(a1, a1, fmaT(a2, a2, eps));
+        pp[r] = fmaT(T(cf[12 + 2 * r]), lo[r], T(cf[13 + 2 * r]) * hi[r]);
+        pm[r] = fmaT(T(cf[18 + 2 * r]), lo[r], T(cf[19 + 2 * r]) * hi[r]);
     }
-    T wp[3], wm[3], sp = T(0), sm = T(0);
+    T sp, sm, np, nm;
     if constexpr (std::is_same<T, double>::value) {
-#pragma unroll
-        for (int r = 0; r < 3; r++) {
-            const T inv = rcp(e[r] * e[r]);
-            wp[r] = T(cf[36 + r]) * inv;
-            wm[r] = T(cf[39 + r]) * inv;
-        }
+        const T s0 = e[0] * e[0], s1 = e[1] * e[1], s2 = e[2] * e[2];
+        const T m0 = s1 * s2, m1 = s0 * s2, m2 = s0 * s1;
+        sp = fmaT(T(cf[24]), m0, fmaT(T(cf[25]), m1, T(cf[26]) * m2));
+        sm = fmaT(T(cf[27]), m0, fmaT(T(cf[28]), m1, T(cf[29]) * m2));
+        np = fmaT(m0, pp[0], fmaT(m1, pp[1], m2 * pp[2]));
+        nm = fmaT(m0, pm[0], fmaT(m1, pm[1], m2 * pm[2]));
     } else {
-        const T emin = __builtin_fminf(e[0], __builtin_fminf(e[1], e[2]));
-#pragma unroll
-        for (int r = 0; r < 3; r++) {
-            const T t = emin * rcp(e[r]);
-            wp[r] = T(cf[36 + r]) * (t * t);
-            wm[r] = T(cf[39 + r]) * (t * t);
-        }
+        const T u0 = fminT(e[1] * rcp(e[0]), T(1.0e9)), u2 = fminT(e[1] * rcp(e[2]), T(1.0e9));
+        const T m0 = u0 * u0, m2 = u2 * u2;
+        sp = fmaT(T(cf[24]), m0, fmaT(T(cf[26]), m2, T(cf[25])));
+        sm = fmaT(T(cf[27]), m0, fmaT(T(cf[29]), m2, T(cf[28])));
+        np = fmaT(m0, pp[0], fmaT(m2, pp[2], pp[1]));
+        nm = fmaT(m0, pm[0], fmaT(m2, pm[2], pm[1]));
     }
-    T np = T(0), nm = T(0);
-#pragma unroll
-    for (int r = 0; r < 3; r++) {
-        sp += wp[r];
-        sm += wm[r];
-        np = fmaT(wp[r], pp[r], np);
-        nm = fmaT(wm[r], pm[r], nm);
-    }
-    plus = np * rcp(sp);
-    minus = nm * rcp(sm);
+    const T r = rcp(sp * sm);
+    plus = fmaT(np, sm * r, v0);
+    minus = fmaT(nm, sp * r, v0);
 }
 
 // Reconstruction along one direction for a cell whose coefficient row is cf
@@ -436,8 +427,8 @@ struct CoefRegs {
     bool on;
     __device__ __forceinline__ T operator[](int i) const { return c[i]; }
 };
-template <class T>
-__device__ __forceinline__ void load_coefs(const double *__restrict__ cf, CoefRegs<T> &r)
+template <class T, class P>
+__device__ __forceinline__ void load_coefs(const P *cf, CoefRegs<T> &r)
 {
     r.on = cf != nullptr;
     if (r.on) {

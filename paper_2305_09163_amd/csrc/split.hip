@@ -204,6 +204,42 @@ constexpr int kXYWaves = ROUTE ? 2
                                : (STRETCH ? (sizeof(T) == 8 ? 2 : 4)
                                           : (sizeof(T) == 8 ? 3 : (KEEP ? 4 : MFC_XY_WAVES32)));
 
+// The coefficient row of a cell in LDS, read by the reconstructions of all its
+// variables.  FP64 holds the smoothness and weight coefficients in registers
+// and reads the increments' twelve per variable: 225 us for the x+y pass of
+// 128^3 cells (all 30 held: 324 with 39 registers spilled; all read per
+// variable: 287; 42 coefficients of values instead of differences: 318), in
+// 16-byte reads (269 us in 8-byte ones).  FP32 has no registers for them at
+// four workgroups per CU.
+template <class T>
+struct RowHeld {
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    static constexpr bool kHeld = sizeof(T) == 8;
+    const T *row;
+    T c[kHeld ? 18 : 1];
+    __device__ __forceinline__ explicit RowHeld(const T *r) : row(r)
+    {
+        if constexpr (kHeld) {
+            if (r) {
+#pragma unroll
+                for (int i = 0; i < 18; i += 2) {
+                    const T2 p = *(const T2 *)(r + (i < 12 ? i : i + 12));
+                    c[i] = p.x;
+                    c[i + 1] = p.y;
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ T operator[](int i) const
+    {
+        if constexpr (kHeld) {
+            if (i < 12 || i >= 24) return c[i < 12 ? i : i - 12];
+        }
+        const T2 p = *(const T2 *)(row + i / 2 * 2);
+        return i % 2 ? p.y : p.x;
+    }
+};
+
 // The x+y pass holds the stage input of its part of the stage combination
 // in registers from the start of each plane and loads q^n late in it
 // (FP64, measured faster), or loads both at its end (FP32, whose five
@@ -293,8 +329,8 @@ __global__ void __launch_bounds__(NT, (kXYWaves<T, ROUTE, STRETCH, KEEP>))
     // for every plane (in registers they spill or cost occupancy); visible
     // after the first barrier below
     constexpr bool kLdsCoef = STRETCH && ORDER == 5;
-    __shared__ T s_cx[kLdsCoef ? (TX + 2) * kStretchCoef : 1];
-    __shared__ T s_cy[kLdsCoef ? (TY + 2) * kStretchCoef : 1];
+    __shared__ __align__(16) T s_cx[kLdsCoef ? (TX + 2) * kStretchCoef : 1];
+    __shared__ __align__(16) T s_cy[kLdsCoef ? (TY + 2) * kStretchCoef : 1];
     if constexpr (kLdsCoef) {
         const bool ux = g.wcoef[0] != nullptr, uy = g.wcoef[1] != nullptr;
         for (int i = tid; i < (TX + 2) * kStretchCoef; i += NT) {
@@ -374,12 +410,12 @@ __global__ void __launch_bounds__(NT, (kXYWaves<T, ROUTE, STRETCH, KEEP>))
                                                  logit_tau, lane);
             }
             if (valid) {
-                const T *cl = kLdsCoef && g.wcoef[0] ? &s_cx[c * kStretchCoef] : nullptr;
+                const RowHeld<T> cl(kLdsCoef && g.wcoef[0] ? &s_cx[c * kStretchCoef] : nullptr);
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
                     const T *st = &s_plane[v][row + H][c + OFF];
                     if (ROUTE && lin) linear5_pair<T>(st[0], st[1], st[2], st[3], st[4], wP[v], s_minus[v][p]);
-                    else if (kLdsCoef && cl) weno5_nonuniform_pair<T>(cl, st[0], st[1], st[2], st[3], st[4], eps, wP[v], s_minus[v][p]);
+                    else if (kLdsCoef && cl.row) weno5_nonuniform_pair<T>(cl, st[0], st[1], st[2], st[3], st[4], eps, wP[v], s_minus[v][p]);
                     else recon_at<ORDER, T>(st, 1, eps, wP[v], s_minus[v][p]);
                 }
             }
@@ -441,13 +477,13 @@ __global__ void __launch_bounds__(NT, (kXYWaves<T, ROUTE, STRETCH, KEEP>))
                                                  lane);
             }
             if (valid) {
-                const T *cl = kLdsCoef && g.wcoef[1] ? &s_cy[r * kStretchCoef] : nullptr;
+                const RowHeld<T> cl(kLdsCoef && g.wcoef[1] ? &s_cy[r * kStretchCoef] : nullptr);
 #pragma unroll
                 for (int v = 0; v < NV; v++) {
                     if (ROUTE && lin)
                         linear5_pair<T>(s_plane[v][r][li], s_plane[v][r + 1][li], s_plane[v][r + 2][li],
                                         s_plane[v][r + 3][li], s_plane[v][r + 4][li], wP[v], s_minus[v][p]);
-                    else if (kLdsCoef && cl)
+                    else if (kLdsCoef && cl.row)
                         weno5_nonuniform_pair<T>(cl, s_plane[v][r][li], s_plane[v][r + 1][li], s_plane[v][r + 2][li],
                                                  s_plane[v][r + 3][li], s_plane[v][r + 4][li], eps, wP[v], s_minus[v][p]);
                     else
@@ -709,7 +745,8 @@ __global__ void __launch_bounds__(kNZT, kZWaves<T>)
                 lin = mlp::smooth_wave(s_mlp, scratch, f, logit_tau, lane);
             }
             CoefRegs<T> cf;   // cell k + S of this window
-            if constexpr (STRETCH && ORDER == 5) load_coefs<T>(coef_row(g, 2, k + S), cf);
+            if constexpr (STRETCH && ORDER == 5)   // the same row for every column: scalar loads
+                load_coefs<T>((const __attribute__((address_space(4))) double *)coef_row(g, 2, k + S), cf);
 #pragma unroll
             for (int v = 0; v < NV; v++) {
                 T st[ORDER];   // the stencil of cell k + S, lowest z first

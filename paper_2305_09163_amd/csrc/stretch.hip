@@ -7,15 +7,18 @@
 // stencil r (cells i-2+r .. i+r) is the derivative of the cubic that
 // interpolates the primitive function V(xi) = int v dxi at the four faces of
 // the stencil (so that p_r has the data as its cell averages); the 5-cell
-// quartic q is built the same way from six faces.  Per cell and direction
-// the table holds, for r = 0, 1, 2 and the stencil's cells j = 0, 1, 2:
-//   [0, 9)    p_r(xi = 1/2)  coefficients   (x_{i+1/2} value)
-//   [9, 18)   p_r(xi = -1/2) coefficients   (x_{i-1/2} value)
-//   [18, 27)  d p_r/d xi at 0               (a1)
-//   [27, 36)  (d^2 p_r/d xi^2)/2 at 0        (a2)
-//   [36, 39)  ideal weights at x_{i+1/2}, [39, 42) at x_{i-1/2},
+// quartic q is built the same way from six faces.  Every quantity of a stencil
+// is a combination of its three values whose coefficients sum to one (p_r at a
+// face) or to zero (its derivatives), and is kept as the two coefficients of
+// the stencil's divided differences, which for p_r gives its increment over
+// v_i.  Per cell and direction the table holds, two each for r = 0, 1, 2:
+//   [0, 6)    d p_r/d xi at 0                         (a1)
+//   [6, 12)   sqrt(13/3) (d^2 p_r/d xi^2)/2 at 0      (a2)
+//   [12, 18)  d_r (p_r - v_i) at x_{i+1/2}
+//   [18, 24)  d_r (p_r - v_i) at x_{i-1/2}
+// and the ideal weights d_r, [24, 27) at x_{i+1/2} and [27, 30) at x_{i-1/2},
 // where sum_r d_r p_r reproduces q at the face; the smoothness indicator
-// sum_l h^{2l-1} int_{I_i} (p_r^(l))^2 is then a1^2 + (13/3) a2^2.
+// sum_l h^{2l-1} int_{I_i} (p_r^(l))^2 is then a1^2 + a2^2.
 #include <cmath>
 #include <vector>
 
@@ -82,7 +85,7 @@ double horner(const double *c, int m, double x)
     return v;
 }
 
-// The 42 coefficients of cell i from the widths of cells i-2 .. i+2.
+// The coefficients of cell i from the widths of cells i-2 .. i+2.
 void cell_coefficients(const double *w, double *out)
 {
     // faces of cells i-2 .. i+2 in xi units (cell i = [-1/2, 1/2])
@@ -95,24 +98,34 @@ void cell_coefficients(const double *w, double *out)
     X[0] = X[1] - w[0] / w[2];
     double q[5][5], pr[5][5];
     reconstruction_basis(X, 5, q);
+    double val[2][3][3];   // coefficients of p_r at x_{i+1/2}, x_{i-1/2}
+    // a combination C of the stencil's values in its two divided differences,
+    // less v_i where the coefficients sum to one
+    auto differences = [](int r, const double *C, double w, double *to) {
+        to[0] = w * (r == 0 ? -C[0] : (r == 1 ? -C[0] : C[1] + C[2]));
+        to[1] = w * (r == 0 ? -(C[0] + C[1]) : C[2]);
+    };
     for (int r = 0; r < 3; r++) {
         reconstruction_basis(X + r, 3, pr);
+        double d1[3], d2[3];
         for (int j = 0; j < 3; j++) {
-            out[3 * r + j] = horner(pr[j], 3, 0.5);
-            out[9 + 3 * r + j] = horner(pr[j], 3, -0.5);
-            out[18 + 3 * r + j] = pr[j][1];
-            out[27 + 3 * r + j] = pr[j][2];
+            val[0][r][j] = horner(pr[j], 3, 0.5);
+            val[1][r][j] = horner(pr[j], 3, -0.5);
+            d1[j] = pr[j][1];
+            d2[j] = pr[j][2];
         }
+        differences(r, d1, 1.0, out + 2 * r);
+        differences(r, d2, std::sqrt(13.0 / 3.0), out + 6 + 2 * r);
     }
-    // cell i-2 appears only in stencil 0, cell i+2 only in stencil 2
-    const double qp0 = horner(q[0], 5, 0.5), qp4 = horner(q[4], 5, 0.5);
-    const double qm0 = horner(q[0], 5, -0.5), qm4 = horner(q[4], 5, -0.5);
-    out[36] = qp0 / out[0];
-    out[38] = qp4 / out[8];
-    out[37] = 1.0 - out[36] - out[38];
-    out[39] = qm0 / out[9];
-    out[41] = qm4 / out[17];
-    out[40] = 1.0 - out[39] - out[41];
+    for (int f = 0; f < 2; f++) {
+        // cell i-2 appears only in stencil 0, cell i+2 only in stencil 2
+        const double x = f == 0 ? 0.5 : -0.5;
+        double *d = out + 24 + 3 * f;
+        d[0] = horner(q[0], 5, x) / val[f][0][0];
+        d[2] = horner(q[4], 5, x) / val[f][2][2];
+        d[1] = 1.0 - d[0] - d[2];
+        for (int r = 0; r < 3; r++) differences(r, val[f][r], d[r], out + 12 + 6 * f + 2 * r);
+    }
 }
 
 }  // namespace
