@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(Shape<NDIM>::NT, 2)
     uint16_t *scratch = (kInFlux ? (uint16_t *)&s_flux[0][0] : s_feat_own) + (threadIdx.x / 64) * 64 * 16;
     const int lane = threadIdx.x % 64;
     if constexpr (ROUTE) {
-        mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, NT);
+        mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, NT, true);
         __syncthreads();
     }
     const T eps = T(g.eps), idx = T(g.inv_dx[0]), idy = T(g.inv_dx[1]), idz = T(g.inv_dx[2]);

@@ -401,6 +401,17 @@ __global__ void __launch_bounds__(kThreads)
     }
 }
 
+// The logit of all-zero features behind a routed network's parameters, by the
+// same tile products as any sample's.
+__global__ void __launch_bounds__(kThreads) k_zero_logit(float *w)
+{
+    __shared__ __align__(16) Params P;
+    stage_params(P, nullptr, w, threadIdx.x, kThreads);
+    __syncthreads();
+    const float z = logit_tile(P, s4{0, 0, 0, 0}, threadIdx.x % 64);
+    if (threadIdx.x == 0) w[NPARAM] = z;
+}
+
 }  // namespace
 }  // namespace mfc
 
@@ -557,8 +568,12 @@ int mfc_set_indicator(mfc_grid *h, const float *params_host, double tau)
     for (int i = 0; i < NPARAM; i++)
         if (!std::isfinite(params_host[i])) return fail(MFC_E_ARG, "non-finite network parameter");
     hipError_t e = hipSuccess;
-    if (!h->mlp) e = hipMalloc((void **)&h->mlp, NPARAM * sizeof(float));
+    if (!h->mlp) e = hipMalloc((void **)&h->mlp, kRoutedWords * sizeof(float));
     if (e == hipSuccess) e = hipMemcpy(h->mlp, params_host, NPARAM * sizeof(float), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_zero_logit, dim3(1), dim3(kThreads), 0, 0, h->mlp);
+        e = hipDeviceSynchronize();   // before work of any stream that reads it
+    }
     if (e != hipSuccess) return hip_status(e, "indicator upload");
     // P > tau  <=>  logit > log(tau / (1 - tau))
     h->logit_tau = tau <= 0.0 ? -INFINITY : (tau >= 1.0 ? INFINITY : (float)std::log(tau / (1.0 - tau)));

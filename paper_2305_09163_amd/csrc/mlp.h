@@ -126,8 +126,14 @@ struct Params {
     s4 a1[2][64];     // W1^T rows 16b + s, k = 4g + t   (layer 1, A operand)
     bf8 a2[2][64];    // W2^T rows 16b + s, k slot t -> unit u(g, t)   (layer 2)
     float b1[NH], b2[NH], w3[NH];
-    float b3, pad[3];
+    float b3;
+    float zero_logit;  // routed kernels: the logit of all-zero features
+    float pad[2];
 };
+
+// Device copy of a routed network: the parameters, then the logit of all-zero
+// features (k_zero_logit).
+constexpr int kRoutedWords = NPARAM + 1;
 
 // Backward-only operand: W2 rows 16b + s (input units), k slot t -> output
 // unit u(g, t), for dH1^T = W2 dZ2^T.
@@ -137,7 +143,9 @@ struct ParamsT {
 
 // Fill P from the flat FP32 parameters; call with all threads of the block,
 // then synchronise.
-__device__ inline void stage_params(Params &P, ParamsT *PT, const float *__restrict__ w, int tid, int nthreads)
+// routed: w is followed by its zero logit.
+__device__ inline void stage_params(Params &P, ParamsT *PT, const float *__restrict__ w, int tid, int nthreads,
+                                    bool routed = false)
 {
     for (int e = tid; e < 2 * 64; e += nthreads) {
         const int b = e / 64, l = e % 64, g = l / 16, s = l % 16;
@@ -163,7 +171,10 @@ __device__ inline void stage_params(Params &P, ParamsT *PT, const float *__restr
         P.b2[e] = w[OB2 + e];
         P.w3[e] = w[OW3 + e];
     }
-    if (tid == 0) P.b3 = w[OB3];
+    if (tid == 0) {
+        P.b3 = w[OB3];
+        if (routed) P.zero_logit = w[NPARAM];
+    }
 }
 
 // Forward state of one tile, as held by one lane (its sample s, its 8 units).
@@ -274,12 +285,19 @@ __device__ __forceinline__ void features(const T *a, const T *rho, const T *p, T
 // Wavefront-cooperative decision: every lane supplies the features of its
 // own sample (64 samples, 4 tiles) and gets back whether its sample's logit
 // exceeds `logit_tau`.  `scratch` is this wavefront's 64 x 16 bf16 LDS area.
-// All 64 lanes must execute this call.
+// All 64 lanes must execute this call; P is a routed network's.
 __device__ __forceinline__ bool smooth_wave(const Params &P, uint16_t *scratch, const uint16_t *feat, float logit_tau,
                                             int lane)
 {
-    uint4 *row = (uint4 *)(scratch + lane * 16);
     const uint32_t *f32 = (const uint32_t *)feat;
+    // A wavefront in a uniform region (gas at rest, the undisturbed side of a
+    // front) has no difference at all: its decision is that of zero features,
+    // bit for bit what the network would give.
+    uint32_t any = 0;
+#pragma unroll
+    for (int k = 0; k < 8; k++) any |= f32[k];
+    if (__ballot(any != 0) == 0) return P.zero_logit > logit_tau;
+    uint4 *row = (uint4 *)(scratch + lane * 16);
     row[0] = make_uint4(f32[0], f32[1], f32[2], f32[3]);
     row[1] = make_uint4(f32[4], f32[5], f32[6], f32[7]);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -35,7 +35,7 @@ __global__ void __launch_bounds__(S2::NT, (kPlaneWaves<T, ROUTE>))
     if (R.loads) read = load_cell2<T>(g, q, x0 + R.lx, y0 + R.ly, mode != 0, inner2<S2>(g, x0, y0), qc);
     const mlp::Params *net = nullptr;
     if constexpr (ROUTE) {   // visible after the tile's first barrier
-        mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, S2::NT);
+        mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, S2::NT, true);
         net = &s_mlp;
     }
     const bool speed = ss.carry != nullptr;

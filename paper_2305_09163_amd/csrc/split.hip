@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(NT, (kXYWaves<T, ROUTE, STRETCH, KEEP>))
     const T cb = T(mode == 2 ? 0.25 : (mode == 3 ? 2.0 / 3.0 : 1.0));
     const int lane = threadIdx.x % 64;
     uint16_t *scratch = (R::in_flux ? (uint16_t *)&s_flux[0][0] : s_feat_own) + (threadIdx.x / 64) * 64 * 16;
-    if constexpr (ROUTE) mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, NT);  // visible after the first barrier
+    if constexpr (ROUTE) mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, NT, true);  // visible after the first barrier
 
     const int tid = threadIdx.x;
     const int tx = tid % TX, ty = tid / TX;
@@ -658,7 +658,7 @@ __global__ void __launch_bounds__(kNZT, kZWaves<T>)
         // reduction: lanes past the last column march a duplicate of it
         // (their maxima are those of that column)
         if constexpr (ROUTE) {
-            mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, NZT);
+            mlp::stage_params(s_mlp, nullptr, mlpw, threadIdx.x, NZT, true);
             __syncthreads();
         }
     } else if (!own) {
