@@ -48,14 +48,14 @@ __device__ __forceinline__ void wave_sync()
 }
 
 // Largest |omega_r - d_r| of WENO5-JS over the three stencils and both faces
-// of the 5-cell stencil s (the weights of Sec. 3.2).  As in the solver's
+// of the 5-cell stencil v (the weights of Sec. 3.2).  As in the solver's
 // weno5_pair, e_r = 3/4 (eps + beta_r) in the divided differences of the
 // stencil and omega_r through common denominators (omega_0 ~ 1 (e_1 e_2)^2
 // and so on, ideal weights times ten), which leaves one reciprocal per face;
 // these are refined to the last place.
-__device__ __forceinline__ double weno_deviation(const double *v, int s, double eps)
+__device__ __forceinline__ double weno_deviation(const double *v, double eps)
 {
-    const double b = v[s] - v[0], a = v[2 * s] - v[s], c = v[3 * s] - v[2 * s], d = v[4 * s] - v[3 * s];
+    const double b = v[1] - v[0], a = v[2] - v[1], c = v[3] - v[2], d = v[4] - v[3];
     const double e3 = 0.75 * eps;
     const double e0 = __builtin_fma(a, __builtin_fma(2.5, a, -2.75 * b), __builtin_fma(b, b, e3));
     const double e1 = __builtin_fma(c, __builtin_fma(-1.25, a, c), __builtin_fma(a, a, e3));
@@ -80,25 +80,33 @@ struct HarvestTile {
     static constexpr int H = 2, NV = 4 + NDIM;
     static constexpr int TX = NDIM == 1 ? 256 : (NDIM == 2 ? 16 : 8), TY = NDIM == 1 ? 1 : (NDIM == 2 ? 16 : 8);
     static constexpr int TZ = NDIM == 3 ? 4 : 1;
-    static constexpr int OY = NDIM >= 2 ? H : 0, OZ = NDIM == 3 ? H : 0;   // LDS position of the first cell
-    static constexpr int PX = TX + 2 * H, PY = TY + 2 * OY, PZ = TZ + 2 * OZ, PLANE = PX * PY * PZ;
-    // halo cells of the x, y and z faces
+    static constexpr int OY = NDIM >= 2 ? H : 0, OZ = NDIM == 3 ? H : 0;   // halo depth in y and z
+    // positions: the tile's cells, then the halo cells of its x, y and z faces
+    // (no edges or corners: three 49 KB workgroups per CU in 3D)
     static constexpr int HX = 2 * H * TY * TZ, HY = 2 * OY * TX * TZ, HZ = 2 * OZ * TX * TY;
+    static constexpr int CELLS = TX * TY * TZ, N = CELLS + HX + HY + HZ;
+    static __device__ __forceinline__ int at(int x, int y, int z)
+    {
+        if (x < 0 || x >= TX) return CELLS + (z * TY + y) * 2 * H + (x < 0 ? x + H : x - TX + H);
+        if (y < 0 || y >= TY) return CELLS + HX + (z * 2 * H + (y < 0 ? y + H : y - TY + H)) * TX + x;
+        if (z < 0 || z >= TZ) return CELLS + HX + HY + ((z < 0 ? z + H : z - TZ + H) * TY + y) * TX + x;
+        return (z * TY + y) * TX + x;
+    }
     static_assert(TX * TY * TZ == kThreads, "one cell per thread");
 };
 
 // 96^3 cells: 192 us with one thread per (cell, direction), five conversions
-// and 99 IEEE divisions per sample; 89 us so (14 reciprocals).
+// and 99 IEEE divisions per sample; 86 us so (14 reciprocals).
 template <int NDIM>
-__global__ void __launch_bounds__(kThreads, 2)
+__global__ void __launch_bounds__(kThreads, 3)
     k_harvest(Grid g, const double *__restrict__ q, uint16_t *__restrict__ X, uint8_t *__restrict__ Y,
               double *__restrict__ D, double sqrt_eps, double threshold, int64_t cells)
 {
     using S = HarvestTile<NDIM>;
     constexpr int NV = S::NV, H = S::H;
     constexpr int E = NV - 2, A = NV - 1;
-    __shared__ double s_w[NV][S::PLANE];   // row E: the pressure's first factor
-    __shared__ double s_ig[S::PLANE];      // its second
+    __shared__ double s_w[NV][S::N];   // row E: the pressure's first factor
+    __shared__ double s_ig[S::N];      // its second
     const int tid = threadIdx.x;
     const int tx = tid % S::TX, ty = (tid / S::TX) % S::TY, tz = tid / (S::TX * S::TY);
     const int tiles_x = (g.n[0] + S::TX - 1) / S::TX, tiles_y = (g.n[1] + S::TY - 1) / S::TY;
@@ -114,7 +122,7 @@ __global__ void __launch_bounds__(kThreads, 2)
         for (int v = 0; v < NV; v++) qc[v] = q[v * g.vstride + o];
         (void)cons_to_prim<NDIM, double>(g, qc, w, pf);
         w[E] = pf[0];
-        const int p = ((k + S::OZ) * S::PY + j + S::OY) * S::PX + i + H;
+        const int p = S::at(i, j, k);
 #pragma unroll
         for (int v = 0; v < NV; v++) s_w[v][p] = w[v];
         s_ig[p] = pf[1];
@@ -146,11 +154,13 @@ __global__ void __launch_bounds__(kThreads, 2)
     const int x = x0 + tx, y = y0 + ty, z = z0 + tz;
     if (x >= g.n[0] || y >= g.n[1] || z >= g.n[2]) return;
     const int64_t c = ((int64_t)z * g.n[1] + y) * g.n[0] + x;
-    const int p = ((tz + S::OZ) * S::PY + ty + S::OY) * S::PX + tx + H;
+    const int p = tid;
 #pragma unroll 1
     for (int d = 0; d < NDIM; d++) {
         const int64_t t = d * cells + c;
-        const int s = d == 0 ? 1 : (d == 1 ? S::PX : S::PX * S::PY), p0 = p - 2 * s;
+        int at[5];   // the stencil's positions
+#pragma unroll
+        for (int j = 0; j < 5; j++) at[j] = S::at(tx + (d == 0 ? j - 2 : 0), ty + (d == 1 ? j - 2 : 0), tz + (d == 2 ? j - 2 : 0));
         // Differences to the centre.  The pressure's are taken before the
         // rounding of the neighbour's product (one FMA), except the one next
         // above the centre: where pressures differ by rounding alone these
@@ -162,7 +172,7 @@ __global__ void __launch_bounds__(kThreads, 2)
         __asm__("" : "+v"(pr2));   // rounded
 #pragma unroll
         for (int j = 0; j < 5; j++) {
-            const int o = p0 + j * s;
+            const int o = at[j];
             dif[0][j] = s_w[A][o] - a2;
             dif[1][j] = (s_w[0][o] + s_w[1][o]) - r2;
             pr[j] = s_w[E][o] * s_ig[o];
@@ -177,7 +187,12 @@ __global__ void __launch_bounds__(kThreads, 2)
         xo[1] = make_uint4(f32[4], f32[5], f32[6], f32[7]);
         double dev = 0.0;
 #pragma unroll
-        for (int v = 0; v < NV; v++) dev = fmax(dev, v == E ? weno_deviation(pr, 1, g.eps) : weno_deviation(&s_w[v][p0], s, g.eps));
+        for (int v = 0; v < NV; v++) {
+            double st[5];
+#pragma unroll
+            for (int j = 0; j < 5; j++) st[j] = v == E ? pr[j] : s_w[v][at[j]];
+            dev = fmax(dev, weno_deviation(st, g.eps));
+        }
         Y[t] = dev < threshold ? 1 : 0;
         if (D) D[t] = dev;
     }
