@@ -244,6 +244,9 @@ int mfc_check(mfc_grid *g, void *stream);
  * launch of mfc_rhs and those of every N-th SSP-RK3 step of mfc_rk3_step and
  * mfc_run, counted from this call (the first step is timed), so that a
  * sample of a long run is timed without events between all its launches.
+ * While it is enabled, 1D runs and steps on small 3D grids, which otherwise
+ * take whole steps or whole stages in one launch, take the kernels it counts
+ * (the same results to rounding).
  * enable < 0 gives MFC_E_ARG.  mfc_kernel_time synchronises, returns the
  * summed duration (ms) and number of timed launches of that slot since the
  * last call for it, and resets them.  slot outside [0, 1] gives MFC_E_ARG. */

@@ -162,6 +162,12 @@ int launch_wavespeed(mfc_grid *h, const void *q, hipStream_t s);
 int launch_rhs_plane(mfc_grid *h, const void *q, const void *q0, void *out, int mode, const StepSize &ss, hipStream_t s);
 // Wave-speed maxima a carrying last stage leaves (one per wavefront of cells).
 int64_t plane_partials(const Grid &g);
+// Small 3D grids of the split path (cube.hip): whether the stages of a
+// handle's steps take one launch each, that launch (modes 1, 2, 3), and the
+// maxima it leaves.
+bool takes_cube(const mfc_grid *h);
+int launch_rhs_cube(mfc_grid *h, const void *q, const void *q0, void *out, int mode, const StepSize &ss, hipStream_t s);
+int64_t cube_partials(const Grid &g);
 // Split path: cfl > 0 reduces the wave speeds of q in the x+y pass and sets
 // the step size before the z pass (the first stage of a CFL step); zmax
 // non-null (a last stage) has the z pass reduce the wave speeds of the state

@@ -557,7 +557,7 @@ int mfc_init_grid(const mfc_grid_desc *desc, mfc_grid **out)
     }
     h->partial_len = std::max<int64_t>(
         kReduceBlocks,
-        desc->ndim == 3 ? std::max(split_xy_blocks(g), split_z_partials(g) + cbc_stored_blocks(g))
+        desc->ndim == 3 ? std::max({split_xy_blocks(g), split_z_partials(g) + cbc_stored_blocks(g), cube_partials(g)})
                         : (desc->ndim == 2 ? plane_partials(g) : line_partials(g)));
     alloc((void **)&h->partial, h->partial_len * 8);
     alloc((void **)&h->scalars, 4 * 8);
@@ -684,7 +684,10 @@ namespace {
 // 2D grids of the fused kernel: so does the last stage's kernel; with
 // characteristic faces, whose boundary pass changes cells after it, every
 // step reduces its own.
-bool steps_by_tiles(const mfc_grid *h) { return h->desc.kernel == MFC_KERNEL_FUSED && h->desc.ndim == 2; }
+bool steps_by_tiles(const mfc_grid *h)
+{
+    return (h->desc.kernel == MFC_KERNEL_FUSED && h->desc.ndim == 2) || takes_cube(h);
+}
 
 bool carries_wavespeed(const mfc_grid *h, double cfl)
 {
@@ -714,7 +717,8 @@ int rk3_step_tiles(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, b
     constexpr int kInStage = 2048;
     int st;
     void *A = h->stage_a, *B = h->stage_b;
-    if (last && (st = fill_ghosts(h, q, s))) return st;
+    const bool cube = h->desc.ndim == 3;   // the split path leaves the ghost cells of q as they are
+    if (last && !cube && (st = fill_ghosts(h, q, s))) return st;
     StepSize first;
     first.cfl = cfl;
     first.dt = dt;
@@ -725,7 +729,7 @@ int rk3_step_tiles(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, b
     if (cfl > 0.0) {
         const int blocks = (int)std::min<int64_t>(kReduceBlocks, blocks_for(h->cells));
         if (!carried_in && (st = wavespeed(h, q, s, blocks))) return st;
-        first.nspeeds = carried_in ? (int)plane_partials(h->g) : blocks;
+        first.nspeeds = !carried_in ? blocks : (int)(cube ? cube_partials(h->g) : plane_partials(h->g));
         if (first.nspeeds > kInStage) {
             launch_step_begin(h, h->partial, first.nspeeds, cfl, 0.0, s);
             first.set = false;
@@ -740,7 +744,9 @@ int rk3_step_tiles(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, b
         if (mode == 1) ss = first;
         else ss.scalars = h->scalars;
         if (carry_out && mode == 3) ss.carry = h->partial;
-        if ((st = launch_rhs_plane(h, in[mode - 1], q, out[mode - 1], mode, ss, s))) return st;
+        st = cube ? launch_rhs_cube(h, in[mode - 1], q, out[mode - 1], mode, ss, s)
+                  : launch_rhs_plane(h, in[mode - 1], q, out[mode - 1], mode, ss, s);
+        if (st) return st;
         if (has_cbc(h) && (st = launch_cbc(h, in[mode - 1], out[mode - 1], mode, 0.0, h->scalars + 1, s))) return st;
     }
     return MFC_OK;
