@@ -256,9 +256,10 @@ __global__ void __launch_bounds__(kReduceThreads) k_wavespeed(Grid g, const T *_
 }
 
 // One block: reduce the partial maxima, then set the step size and advance
-// the accumulated time.  scalars = [smax, dt, t].  Sixteen wavefronts with
-// four loads in flight per lane: the launch is the latency of its loads
-// (20480 partials of a 256^3 grid: 27 us with four wavefronts and one load).
+// the accumulated time.  scalars = [smax, dt, t].  The launch is the latency of
+// its loads: four in flight per lane, predicated, so that up to 1024 maxima
+// (four wavefronts) or 4096 (sixteen) take one round trip (297 maxima 3.5 us,
+// 4.6 in two rounds; 20480 of a 256^3 grid 5 us, 27 with one load per lane).
 constexpr int kBeginThreads = 1024;
 __global__ void __launch_bounds__(kBeginThreads) k_step_begin(const double *__restrict__ partial, int nblocks,
                                                               double cfl, double dt_fixed, double dxmin,
@@ -268,14 +269,13 @@ __global__ void __launch_bounds__(kBeginThreads) k_step_begin(const double *__re
     __shared__ double red[kBeginThreads / 64];
     double m = 0.0;
     if (partial) {
-        int b = threadIdx.x;
-        for (; b + 3 * (int)blockDim.x < nblocks; b += 4 * blockDim.x) {
+        const int step = blockDim.x;
+        for (int b = threadIdx.x; b < nblocks; b += 4 * step) {
             double p[4];
 #pragma unroll
-            for (int j = 0; j < 4; j++) p[j] = partial[b + j * blockDim.x];
+            for (int j = 0; j < 4; j++) p[j] = b + j * step < nblocks ? partial[b + j * step] : 0.0;
             m = __builtin_fmax(m, __builtin_fmax(__builtin_fmax(p[0], p[1]), __builtin_fmax(p[2], p[3])));
         }
-        for (; b < nblocks; b += blockDim.x) m = __builtin_fmax(m, partial[b]);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = __builtin_fmax(m, __shfl_xor(m, o, 64));
@@ -419,7 +419,7 @@ void fill_ghosts_t(mfc_grid *h, T *q, hipStream_t s)
 
 void launch_step_begin(mfc_grid *h, const double *partial, int nblocks, double cfl, double dt, hipStream_t s)
 {
-    const int threads = nblocks > 2048 ? kBeginThreads : 256;
+    const int threads = nblocks > 1024 ? kBeginThreads : 256;   // one round of loads up to 4096 maxima
     hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(threads), 0, s, partial, nblocks, cfl, dt, h->g.dxmin,
                        h->scalars, h->dt_out);
 }
