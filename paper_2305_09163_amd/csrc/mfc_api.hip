@@ -681,9 +681,9 @@ namespace {
 // characteristic faces the boundary pass, which changes the z faces' cells
 // after the z pass, reduces those cells itself.
 //
-// 2D grids of the fused kernel: so does the last stage's kernel; with
-// characteristic faces, whose boundary pass changes cells after it, every
-// step reduces its own.
+// 2D grids of the fused kernel and small 3D grids of the split path: so does
+// the last stage's kernel; with characteristic faces (2D), whose boundary pass
+// changes cells after it, every step reduces its own.
 bool steps_by_tiles(const mfc_grid *h)
 {
     return (h->desc.kernel == MFC_KERNEL_FUSED && h->desc.ndim == 2) || takes_cube(h);
@@ -707,7 +707,8 @@ int rk3_step_launches(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s
 
 // The same on a grid whose stage kernels read past the faces through the
 // boundary rule and set the step size themselves.  The ghost cells of q are
-// those a fill before every right-hand side leaves: of the last step's q^n.
+// those a fill before every right-hand side leaves, of the last step's q^n (2D;
+// the split path leaves them as they are).
 int rk3_step_tiles(mfc_grid *h, void *q, double cfl, double dt, hipStream_t s, bool carried_in, bool carry_out, bool last)
 {
     // Up to this many maxima (four per tile) every workgroup of the first
