@@ -165,6 +165,8 @@ __device__ __forceinline__ T sound2(T Gam, T Pi, T rho, T p)
 // Positive and finite: one class test (positive normal or denormal).
 __device__ __forceinline__ bool positive(double x) { return __builtin_amdgcn_class(x, 0x180); }
 __device__ __forceinline__ bool positive(float x) { return __builtin_amdgcn_classf(x, 0x180); }
+// Normal (of either sign): neither zero, denormal, infinite nor NaN.
+__device__ __forceinline__ bool normal(double x) { return __builtin_amdgcn_class(x, 0x108); }
 
 template <class T>
 __device__ __forceinline__ bool nonphysical(T rho, T c2)
@@ -394,8 +396,11 @@ __device__ __forceinline__ void recon_pair(T vm2, T vm1, T v0, T vp1, T vp2, T e
 // theirs).  Through common denominators in FP64 and relative to the central
 // stencil in FP32, as weno5_pair: 59 instructions and one reciprocal per value
 // in FP64 (values instead of increments and a reciprocal per weight: 80 and
-// five).  CF is the row in memory, or a copy of it in registers (one load per
-// cell for all its variables).
+// five).  The one reciprocal is of an eighth power of the smoothness
+// indicators; where that leaves the normal numbers (an epsilon below 1e-38 in
+// a uniform region, indicators above 1e38) every weight takes its own, of a
+// square, as the definition does.  CF is the row in memory, or a copy of it in
+// registers (one load per cell for all its variables).
 template <class T, class CF>
 __device__ __forceinline__ void weno5_nonuniform_pair(const CF &cf, T vm2, T vm1, T v0, T vp1, T vp2, T eps, T &plus,
                                                       T &minus)
@@ -419,6 +424,16 @@ __device__ __forceinline__ void weno5_nonuniform_pair(const CF &cf, T vm2, T vm1
         sm = fmaT(T(cf[27]), m0, fmaT(T(cf[28]), m1, T(cf[29]) * m2));
         np = fmaT(m0, pp[0], fmaT(m1, pp[1], m2 * pp[2]));
         nm = fmaT(m0, pm[0], fmaT(m1, pm[1], m2 * pm[2]));
+        if (__builtin_expect(!normal(sp * sm), 0)) {
+            T i[3];
+#pragma unroll
+            for (int r = 0; r < 3; r++) i[r] = rcp(e[r] * e[r]);
+            sp = fmaT(T(cf[24]), i[0], fmaT(T(cf[25]), i[1], T(cf[26]) * i[2]));
+            sm = fmaT(T(cf[27]), i[0], fmaT(T(cf[28]), i[1], T(cf[29]) * i[2]));
+            plus = fmaT(fmaT(i[0], pp[0], fmaT(i[1], pp[1], i[2] * pp[2])), rcp(sp), v0);
+            minus = fmaT(fmaT(i[0], pm[0], fmaT(i[1], pm[1], i[2] * pm[2])), rcp(sm), v0);
+            return;
+        }
     } else {
         const T u0 = fminT(e[1] * rcp(e[0]), T(1.0e9)), u2 = fminT(e[1] * rcp(e[2]), T(1.0e9));
         const T m0 = u0 * u0, m2 = u2 * u2;

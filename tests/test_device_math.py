@@ -1,0 +1,68 @@
+"""The device building blocks of physics.h (reconstruction and HLLC flux),
+built for the CPU with stand-ins for the hardware's estimates
+(tests/device_math), against the oracle's at the ends of their ranges: where
+a product of several small or large factors leaves the range of its type
+although the result does not."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2305_09163_amd import workloads as W
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2305_09163_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def dm(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("device_math") / "device_math.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-ffp-contract=off", "-w", "-shared", "-fPIC",
+                    "-I" + os.path.join(HERE, "device_math"), "-I" + CSRC, "-o", lib,
+                    os.path.join(HERE, "device_math", "harness.cpp")], check=True)
+    return ctypes.CDLL(lib)
+
+
+def _p(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+
+def uniform_row():
+    """The coefficient row of a cell among cells of equal widths: a1, a2
+    (times sqrt(13/3)) and the weighted increments at either face in the
+    differences of each stencil, then the ideal weights."""
+    k = np.sqrt(13.0 / 3.0) / 2.0
+    inc = lambda d, t: [d / 6.0 * x for x in t]
+    return np.array([-0.5, 1.5, 0.5, 0.5, 1.5, -0.5] + [-k, k] * 3
+                    + inc(0.1, (-2, 5)) + inc(0.6, (1, 2)) + inc(0.3, (4, -1))
+                    + inc(0.3, (1, -4)) + inc(0.6, (-2, -1)) + inc(0.1, (-5, 2))
+                    + [0.1, 0.6, 0.3, 0.3, 0.6, 0.1])
+
+
+STENCILS = {
+    "constant": (3.0, 3.0, 3.0, 3.0, 3.0),
+    "smooth": (1.0, 1.1, 1.25, 1.3, 1.28),
+    "jump": (1.0, 1.0, 1.0, 1.0e9, 1.0e9),
+    "far jump": (1.0, 1.0, 1.0, 1.0, 1.0e9),
+    "tails": (0.0, 1.0e-46, 3.0e-46, 2.0e-44, 1.0e-43),
+    "huge": (1.0e31, 2.0e31, 2.5e31, 9.0e31, 9.5e31),
+}
+
+
+@pytest.mark.parametrize("eps", [1e-6, 1e-40, 1e-100, 1e-150])
+@pytest.mark.parametrize("name", sorted(STENCILS))
+def test_weno5_nonuniform_fp64(dm, name, eps):
+    """Every stencil whose (eps + beta_r)^2 are FP64 numbers, as the
+    definition needs.  Both sides round the differences, a1 and a2 once or
+    twice and the weights a few times: 64 roundings of the largest value."""
+    s, row = np.array(STENCILS[name]), uniform_row()
+    assert dm.dm_coefs() == row.size
+    plus, minus = np.empty(1), np.empty(1)
+    dm.dm_weno5_nonuniform(_p(row), _p(s), ctypes.c_double(eps), _p(plus), _p(minus))
+    ref = oracle.weno5_nonuniform(np.ones(5), s, eps)
+    # the face value is a sum of candidates, each within a few of the largest value
+    tol = 64 * np.finfo(np.float64).eps * np.abs(s).max()
+    assert abs(plus[0] - ref[0]) <= tol and abs(minus[0] - ref[1]) <= tol, (plus, minus, ref)
