@@ -583,25 +583,27 @@ __device__ __forceinline__ bool hllc(const Grid &g, const T *wL, const T *wR, T 
     for (int m = 0; m < NDIM; m++) F[2 + m] = (m == DIR) ? fmaT(mn, un, p) : mn * w[2 + m];
     F[E] = (En + p) * un;
 
-    // star correction s_K (q*_K - q_K), with xi - 1 = (s* - u)/(s_K - s*)
-    const T ism = rcp(sK - sS);
-    const T xim1 = (sS - un) * ism;
+    // star correction s_K (q*_K - q_K), with xi - 1 = (s* - u)/(s_K - s*) and
+    // xi s* - u = (xi - 1) s* + (s* - u).  Outside the fan's star region it is
+    // formed from the side's own velocity with a divisor of one, and every row
+    // of it is zero: s* and s_K - s* may be no numbers there (signal speeds
+    // that round to the velocity).
+    uf = star ? sS : un;
+    const T ism = rcp(star ? sK - sS : T(1));
+    const T du = uf - un;
+    const T xim1 = du * ism;
     const T xi = (sK - un) * ism;
     T dq[NV - 1];
     const T xr = xim1 * rho;
     dq[0] = xim1 * w[0];
     dq[1] = xim1 * w[1];
 #pragma unroll
-    for (int m = 0; m < NDIM; m++) dq[2 + m] = (m == DIR) ? rho * fmaT(xi, sS, -un) : xr * w[2 + m];
+    for (int m = 0; m < NDIM; m++) dq[2 + m] = (m == DIR) ? rho * fmaT(xim1, uf, du) : xr * w[2 + m];
     // xi (s* - u)(rho s* + p/(s_K - u)) = (s* - u)(xi rho s* + p/(s_K - s*))
-    dq[E] = xim1 * En + (sS - un) * fmaT(xi * rho, sS, p * ism);
-    // outside the fan's star region the correction has weight zero (one
-    // select in place of one per row)
-    const T ws = star ? sK : T(0);
+    dq[E] = xim1 * En + du * fmaT(xi * rho, uf, p * ism);
 #pragma unroll
-    for (int v = 0; v < NV - 1; v++) F[v] = fmaT(ws, dq[v], F[v]);
+    for (int v = 0; v < NV - 1; v++) F[v] = fmaT(sK, dq[v], F[v]);
 
-    uf = star ? sS : un;
     F[A] = w[A] * uf;
     return bad;
 }

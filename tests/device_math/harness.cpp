@@ -14,3 +14,24 @@ void dm_weno5_nonuniform(const double *row, const double *s, double eps, double 
 }
 
 }  // extern "C"
+
+static Grid fluids(const double *gamma, const double *pi_inf)
+{
+    Grid g{};
+    g.g1 = 1.0 / (gamma[0] - 1.0);
+    g.g2 = 1.0 / (gamma[1] - 1.0);
+    g.h1 = gamma[0] * pi_inf[0] * g.g1;
+    g.h2 = gamma[1] * pi_inf[1] * g.g2;
+    return g;
+}
+
+// One-dimensional HLLC flux (5 rows) and face velocity; whether a side is
+// non-physical.
+extern "C" int dm_hllc(const double *gamma, const double *pi_inf, const double *wL, const double *wR, double *F, double *uf)
+{
+    return hllc<1, 0, double>(fluids(gamma, pi_inf), wL, wR, F, *uf);
+}
+extern "C" int dm_hllc_f(const double *gamma, const double *pi_inf, const float *wL, const float *wR, float *F, float *uf)
+{
+    return hllc<1, 0, float>(fluids(gamma, pi_inf), wL, wR, F, *uf);
+}

@@ -66,3 +66,29 @@ def test_weno5_nonuniform_fp64(dm, name, eps):
     # the face value is a sum of candidates, each within a few of the largest value
     tol = 64 * np.finfo(np.float64).eps * np.abs(s).max()
     assert abs(plus[0] - ref[0]) <= tol and abs(minus[0] - ref[1]) <= tol, (plus, minus, ref)
+
+
+GAMMA, PI_INF = np.array([4.4, 1.4]), np.array([0.0, 0.0])
+
+
+def hllc(dm, dtype, wL, wR):
+    F, uf = np.empty(5, dtype), np.empty(1, dtype)
+    f = dm.dm_hllc if dtype == np.float64 else dm.dm_hllc_f
+    bad = f(_p(GAMMA), _p(PI_INF), _p(np.array(wL, dtype)), _p(np.array(wR, dtype)), _p(F), _p(uf))
+    spec = W.GridSpec(ndim=1, n=(8,), gamma=tuple(GAMMA), pi_inf=tuple(PI_INF))
+    # the oracle's, from the values as rounded to dtype
+    ref, uref, st = oracle.hllc(spec, 0, np.array(wL, dtype).astype(float), np.array(wR, dtype).astype(float))
+    return (F.astype(float), float(uf[0]), bad), (ref, uref, st)
+
+
+@pytest.mark.parametrize("dtype,u,p", [(np.float64, 1.0e9, 1.0e-18), (np.float32, 1.0e4, 1.0e-9)])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_hllc_supersonic_with_no_fan(dm, dtype, u, p, sign):
+    """A sound speed below half a unit in the last place of the velocity: both
+    signal speeds round to the velocity, s* is no number, and the flux is that
+    of the upwind side."""
+    L, R = [0.25, 0.75, sign * u, p, 0.25], [0.5, 1.0, sign * u, 2.0 * p, 0.25]
+    (F, uf, bad), (ref, uref, st) = hllc(dm, dtype, L, R)
+    assert not bad and st == oracle.OK and uf == uref
+    tol = 8 * np.finfo(dtype).eps   # products of three or four factors
+    assert (np.abs(F - ref) <= tol * np.abs(ref)).all(), (F, ref)
