@@ -52,8 +52,12 @@ __device__ __forceinline__ void wave_sync()
 // weno5_pair, e_r = 3/4 (eps + beta_r) in the divided differences of the
 // stencil and omega_r through common denominators (omega_0 ~ 1 (e_1 e_2)^2
 // and so on, ideal weights times ten), which leaves one reciprocal per face;
-// these are refined to the last place.
-__device__ __forceinline__ double weno_deviation(const double *v, double eps)
+// these are refined to the last place.  The denominators are fourth powers
+// of e_r; where they leave the normal numbers (differences above 1e38, or below
+// 1e-38 with an epsilon to match), `rare` is set and the caller takes the
+// weights as they are defined instead (BY_SQUARES).
+template <bool BY_SQUARES = false>
+__device__ __forceinline__ double weno_deviation(const double *v, double eps, bool &rare)
 {
     const double b = v[1] - v[0], a = v[2] - v[1], c = v[3] - v[2], d = v[4] - v[3];
     const double e3 = 0.75 * eps;
@@ -61,9 +65,24 @@ __device__ __forceinline__ double weno_deviation(const double *v, double eps)
     const double e1 = __builtin_fma(c, __builtin_fma(-1.25, a, c), __builtin_fma(a, a, e3));
     const double e2 = __builtin_fma(c, __builtin_fma(2.5, c, -2.75 * d), __builtin_fma(d, d, e3));
     const double s0 = e0 * e0, s1 = e1 * e1, s2 = e2 * e2;
+    if constexpr (BY_SQUARES) {
+        const double s[3] = {s0, s1, s2}, d[3] = {0.1, 0.6, 0.3};
+        double ap[3], am[3], dev = 0.0;
+#pragma unroll
+        for (int r = 0; r < 3; r++) {
+            ap[r] = d[r] / s[r];
+            am[r] = d[2 - r] / s[r];
+        }
+        const double sp = ap[0] + ap[1] + ap[2], sm = am[0] + am[1] + am[2];
+#pragma unroll
+        for (int r = 0; r < 3; r++) dev = fmax(dev, fmax(fabs(ap[r] / sp - d[r]), fabs(am[r] / sm - d[2 - r])));
+        return dev;
+    }
     const double m0 = s1 * s2, m1 = 6.0 * (s0 * s2), m2 = s0 * s1;
-    const double rp = divisor(__builtin_fma(3.0, m2, m0 + m1));   // + face: weights 1, 6, 3
-    const double rm = divisor(__builtin_fma(3.0, m0, m1 + m2));   // - face: weights 3, 6, 1
+    const double sp = __builtin_fma(3.0, m2, m0 + m1);   // + face: weights 1, 6, 3
+    const double sm = __builtin_fma(3.0, m0, m1 + m2);   // - face: weights 3, 6, 1
+    rare |= !normal(sp) || !normal(sm);
+    const double rp = divisor(sp), rm = divisor(sm);
     double dev = fmax(fabs(__builtin_fma(m0, rp, -0.1)), fabs(__builtin_fma(m1, rp, -0.6)));
     dev = fmax(dev, fabs(__builtin_fma(3.0 * m2, rp, -0.3)));
     dev = fmax(dev, fabs(__builtin_fma(3.0 * m0, rm, -0.3)));
@@ -186,12 +205,23 @@ __global__ void __launch_bounds__(kThreads, 3)
         xo[0] = make_uint4(f32[0], f32[1], f32[2], f32[3]);
         xo[1] = make_uint4(f32[4], f32[5], f32[6], f32[7]);
         double dev = 0.0;
+        bool rare = false;
 #pragma unroll
         for (int v = 0; v < NV; v++) {
             double st[5];
 #pragma unroll
             for (int j = 0; j < 5; j++) st[j] = v == E ? pr[j] : s_w[v][at[j]];
-            dev = fmax(dev, weno_deviation(st, g.eps));
+            dev = fmax(dev, weno_deviation(st, g.eps, rare));
+        }
+        if (__builtin_expect(rare, 0)) {
+            dev = 0.0;
+#pragma unroll 1
+            for (int v = 0; v < NV; v++) {
+                double st[5];
+#pragma unroll
+                for (int j = 0; j < 5; j++) st[j] = v == E ? pr[j] : s_w[v][at[j]];
+                dev = fmax(dev, weno_deviation<true>(st, g.eps, rare));
+            }
         }
         Y[t] = dev < threshold ? 1 : 0;
         if (D) D[t] = dev;
