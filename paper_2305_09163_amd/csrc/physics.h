@@ -295,9 +295,14 @@ __device__ __forceinline__ T alpha_source(const Grid &g, T alpha1, T p)
 //     strong jumps, so the weights are taken relative to the central
 //     stencil's, a_r ~ d_r ((eps + beta_1)/(eps + beta_r))^2 and a_1 ~ d_1
 //     (two reciprocals; relative to the smallest (eps + beta), three), with
-//     the ratios held to 1e9: the central stencil then weighs less than
-//     1e-17, beyond the last place of a sum that holds the others.  47
-//     instructions and 3 reciprocals per value where there were 49 and 4.
+//     everything scaled by 2^-36 and the ratios held to 2^48, which together
+//     keep the product of the two sums in range and a weight that should
+//     vanish at 2^-96 of the others: such a stencil holds a jump, and
+//     increments as large (with ratios held to 1e9 and no scale, 1e-18: a
+//     jump of 1e10 times the value showed in its last place).  A ratio of two
+//     indicators that overflowed counts as zero: the outer stencil holds the
+//     jump.  48 instructions and 3 reciprocals per value where there were 49
+//     and 4.
 //     Against 80-bit arithmetic over smooth, random and jumping stencils
 //     (0 .. 1e9) the largest error is 2.7e-7 of the stencil's scale (3.0e-7
 //     relative to the smallest), the mean the same or smaller on each.
@@ -323,6 +328,11 @@ __device__ __forceinline__ void weno5_pair(double vm2, double vm1, double v0, do
     minus = __builtin_fma(nm, sp * r, v0);
 }
 
+// The ratio of the central stencil's indicator, times kRatioScale, to another
+// (the median of a NaN and two numbers is the smaller of these).
+constexpr float kRatioScale = 0x1p-18f, kCentral = kRatioScale * kRatioScale;
+__device__ __forceinline__ float weight_ratio(float e1, float e) { return __builtin_amdgcn_fmed3f(e1 * rcp(e), 0.0f, 0x1p30f); }
+
 __device__ __forceinline__ void weno5_pair(float vm2, float vm1, float v0, float vp1, float vp2, float eps,
                                            float &plus, float &minus)
 {
@@ -331,13 +341,14 @@ __device__ __forceinline__ void weno5_pair(float vm2, float vm1, float v0, float
     const float e0 = __builtin_fmaf(a, __builtin_fmaf(2.5f, a, -2.75f * b), __builtin_fmaf(b, b, e3));
     const float e1 = __builtin_fmaf(c, __builtin_fmaf(-1.25f, a, c), __builtin_fmaf(a, a, e3));
     const float e2 = __builtin_fmaf(c, __builtin_fmaf(2.5f, c, -2.75f * d), __builtin_fmaf(d, d, e3));
-    const float u0 = __builtin_fminf(e1 * rcp(e0), 1.0e9f), u2 = __builtin_fminf(e1 * rcp(e2), 1.0e9f);
+    const float s1 = kRatioScale * e1, u0 = weight_ratio(s1, e0), u2 = weight_ratio(s1, e2);
+    constexpr float k6 = 6.0f * kCentral, k12 = 12.0f * kCentral;
     const float m0 = u0 * u0, m2 = u2 * u2, t0 = 3.0f * m0, t2 = 3.0f * m2;
-    const float sp = (m0 + 6.0f) + t2, sm = (m2 + 6.0f) + t0;
+    const float sp = (m0 + k6) + t2, sm = (m2 + k6) + t0;
     const float np = __builtin_fmaf(t2, __builtin_fmaf(4.0f, c, -d),
-                                   __builtin_fmaf(m0, __builtin_fmaf(5.0f, a, -2.0f * b), __builtin_fmaf(12.0f, c, 6.0f * a)));
+                                   __builtin_fmaf(m0, __builtin_fmaf(5.0f, a, -2.0f * b), __builtin_fmaf(k12, c, k6 * a)));
     const float nm = __builtin_fmaf(m2, __builtin_fmaf(2.0f, d, -5.0f * c),
-                                   __builtin_fmaf(t0, __builtin_fmaf(-4.0f, a, b), -__builtin_fmaf(12.0f, a, 6.0f * c)));
+                                   __builtin_fmaf(t0, __builtin_fmaf(-4.0f, a, b), -__builtin_fmaf(k12, a, k6 * c)));
     const float r = rcp((6.0f * sp) * sm);
     plus = __builtin_fmaf(np, sm * r, v0);
     minus = __builtin_fmaf(nm, sp * r, v0);
@@ -435,12 +446,12 @@ __device__ __forceinline__ void weno5_nonuniform_pair(const CF &cf, T vm2, T vm1
             return;
         }
     } else {
-        const T u0 = fminT(e[1] * rcp(e[0]), T(1.0e9)), u2 = fminT(e[1] * rcp(e[2]), T(1.0e9));
+        const T s1 = kRatioScale * e[1], u0 = weight_ratio(s1, e[0]), u2 = weight_ratio(s1, e[2]);
         const T m0 = u0 * u0, m2 = u2 * u2;
-        sp = fmaT(T(cf[24]), m0, fmaT(T(cf[26]), m2, T(cf[25])));
-        sm = fmaT(T(cf[27]), m0, fmaT(T(cf[29]), m2, T(cf[28])));
-        np = fmaT(m0, pp[0], fmaT(m2, pp[2], pp[1]));
-        nm = fmaT(m0, pm[0], fmaT(m2, pm[2], pm[1]));
+        sp = fmaT(T(cf[24]), m0, fmaT(T(cf[26]), m2, kCentral * T(cf[25])));
+        sm = fmaT(T(cf[27]), m0, fmaT(T(cf[29]), m2, kCentral * T(cf[28])));
+        np = fmaT(m0, pp[0], fmaT(m2, pp[2], kCentral * pp[1]));
+        nm = fmaT(m0, pm[0], fmaT(m2, pm[2], kCentral * pm[1]));
     }
     const T r = rcp(sp * sm);
     plus = fmaT(np, sm * r, v0);

@@ -12,6 +12,15 @@ void dm_weno5_nonuniform(const double *row, const double *s, double eps, double 
 {
     weno5_nonuniform_pair<double>(row, s[0], s[1], s[2], s[3], s[4], eps, *plus, *minus);
 }
+void dm_weno5_nonuniform_f(const double *row, const float *s, float eps, float *plus, float *minus)
+{
+    weno5_nonuniform_pair<float>(row, s[0], s[1], s[2], s[3], s[4], eps, *plus, *minus);
+}
+
+void dm_weno5_f(const float *s, float eps, float *plus, float *minus)
+{
+    weno5_pair(s[0], s[1], s[2], s[3], s[4], eps, *plus, *minus);
+}
 
 }  // extern "C"
 

@@ -39,3 +39,10 @@ static inline bool in_class(T x, int mask)
 }
 static inline bool __builtin_amdgcn_class(double x, int mask) { return in_class(x, mask); }
 static inline bool __builtin_amdgcn_classf(float x, int mask) { return in_class(x, mask); }
+
+// median of three; with a NaN among them the smallest of the others
+static inline float __builtin_amdgcn_fmed3f(float a, float b, float c)
+{
+    if (std::isnan(a) || std::isnan(b) || std::isnan(c)) return std::fmin(a, std::fmin(b, c));
+    return std::fmax(std::fmin(a, b), std::fmin(std::fmax(a, b), c));
+}

@@ -68,6 +68,26 @@ def test_weno5_nonuniform_fp64(dm, name, eps):
     assert abs(plus[0] - ref[0]) <= tol and abs(minus[0] - ref[1]) <= tol, (plus, minus, ref)
 
 
+@pytest.mark.parametrize("uniform", [True, False])
+@pytest.mark.parametrize("s", [(1, 1, 1, 1e20, 1e20), (1e20, 1e20, 1, 1, 1), (1, 1, 1, 1, 1e25), (1e25, 1, 1, 1, 1),
+                               (1, 1.5, 2, 1e22, 3e22), (3e22, 1e22, 2, 1.5, 1), (1, 1, 1, 2e19, 1), (1, 1.5, 2, 1e9, 1e9),
+                               (1, 1.5, 2, 1e13, 1e13), (2e18, 1e18, 2, 1.5, 1)])
+def test_weno5_fp32_beside_a_jump(dm, s, uniform):
+    """A smooth outer stencil beside differences whose squares overflow FP32:
+    the face values are that stencil's, each a few roundings of its own values
+    of order one (the jump itself only to its own last place)."""
+    s = np.array(s, np.float32)
+    plus, minus = np.empty(1, np.float32), np.empty(1, np.float32)
+    if uniform:
+        dm.dm_weno5_f(_p(s), ctypes.c_float(1e-6), _p(plus), _p(minus))
+    else:
+        dm.dm_weno5_nonuniform_f(_p(uniform_row()), _p(s), ctypes.c_float(1e-6), _p(plus), _p(minus))
+    ref = oracle.weno5(s.astype(float), float(np.float32(1e-6)))[:2]
+    assert max(np.abs(ref)) < 10
+    for got, want in zip((plus[0], minus[0]), ref):
+        assert abs(got - want) <= 32 * np.finfo(np.float32).eps, (got, want)
+
+
 GAMMA, PI_INF = np.array([4.4, 1.4]), np.array([0.0, 0.0])
 
 
