@@ -167,6 +167,14 @@ __device__ __forceinline__ bool positive(double x) { return __builtin_amdgcn_cla
 __device__ __forceinline__ bool positive(float x) { return __builtin_amdgcn_classf(x, 0x180); }
 // Normal (of either sign): neither zero, denormal, infinite nor NaN.
 __device__ __forceinline__ bool normal(double x) { return __builtin_amdgcn_class(x, 0x108); }
+// Positive and normal.
+__device__ __forceinline__ bool positive_normal(double x) { return __builtin_amdgcn_class(x, 0x100); }
+__device__ __forceinline__ bool positive_normal(float x) { return __builtin_amdgcn_classf(x, 0x100); }
+// Zero, denormal or infinite.
+__device__ __forceinline__ bool out_of_range(double x) { return __builtin_amdgcn_class(x, 0x2f4); }
+__device__ __forceinline__ bool out_of_range(float x) { return __builtin_amdgcn_classf(x, 0x2f4); }
+// Whether b holds in any active lane of the wavefront.
+__device__ __forceinline__ bool any_lane(bool b) { return __ballot(b) != 0; }
 
 template <class T>
 __device__ __forceinline__ bool nonphysical(T rho, T c2)
@@ -174,28 +182,43 @@ __device__ __forceinline__ bool nonphysical(T rho, T c2)
     return !positive(rho) || !positive(c2);
 }
 
-// Frozen mixture sound speed itself, c = N / sqrt(N G) with N = (Gamma + 1) p + Pi
-// and G = Gamma rho, so that one reciprocal square root serves the quotient
-// and the root.  Double: the estimate y ~ 1/sqrt(N G) (about 24 bits) gives
-// c ~ N y, then two corrections c <- c + (N - c^2 G) y/2, each doubling the
-// correct bits: 12 instructions and one estimate where sqrtT(sound2()) takes
-// 15 and two (x+y pass of 128^3 cells FP64 131.5 -> 129.1 us, its spilled
-// registers gone).  Single: the estimate's 1 ulp.  bad: c^2 is not positive and
-// finite (N G has its sign).
-__device__ __forceinline__ double sound_speed(double Gam, double Pi, double rho, double p, bool &bad)
+// Frozen mixture sound speed itself; bad: c^2 is not positive and finite.  From
+// N = (Gamma + 1) p + Pi, G = Gamma rho and X = N G as c = N / sqrt(X), so that
+// one reciprocal square root serves the quotient and the root.  Double: the
+// estimate y ~ 1/sqrt(X) (about 24 bits) gives c ~ N y, then two corrections
+// c <- c + (N - c^2 G) y/2, each doubling the correct bits: 12 instructions and
+// one estimate where sqrtT(sound2()) takes 15 and two (x+y pass of 128^3 cells
+// FP64 131.5 -> 129.1 us, its spilled registers gone).  Single: the estimate's
+// 1 ulp.
+//   The product of a pressure and a density can leave the type's range where
+// neither does nor their quotient (FP32: below 1e-38); such a lane takes the
+// quotient and its root.  Branches of whole wavefronts, the first on the one
+// test that physical states pass (a branch of lanes, or a second test outside
+// it, lengthens a 1D stage by 2 to 4 %); negative products and NaN are
+// non-physical and leave by the second.
+__device__ __forceinline__ double sound_speed_of(double N, double G, double X)
 {
-    const double N = __builtin_fma(Gam + 1.0, p, Pi), G = Gam * rho, X = N * G;
-    bad = !positive(X);
     const double y = __builtin_amdgcn_rsq(X), h = 0.5 * y;
     double c = N * y;
     c = __builtin_fma(__builtin_fma(-c, c * G, N), h, c);
     return __builtin_fma(__builtin_fma(-c, c * G, N), h, c);
 }
-__device__ __forceinline__ float sound_speed(float Gam, float Pi, float rho, float p, bool &bad)
+__device__ __forceinline__ float sound_speed_of(float N, float, float X) { return N * __builtin_amdgcn_rsqf(X); }
+template <class T>
+__device__ __forceinline__ T sound_speed(T Gam, T Pi, T rho, T p, bool &bad)
 {
-    const float N = __builtin_fmaf(Gam + 1.0f, p, Pi), X = N * (Gam * rho);
-    bad = !positive(X);
-    return N * __builtin_amdgcn_rsqf(X);
+    const T N = fmaT(Gam + T(1), p, Pi), G = Gam * rho, X = N * G;
+    T c = sound_speed_of(N, G, X);
+    bad = !positive_normal(X);
+    if (__builtin_expect(any_lane(bad), 0)) {
+        const bool far = out_of_range(X);
+        if (any_lane(far)) {
+            const T c2 = N * rcp(G);
+            c = far ? sqrtT(c2) : c;
+            bad = far ? !positive(c2) : bad;
+        }
+    }
+    return c;
 }
 
 // Conservative -> primitive for one cell; returns true if non-physical

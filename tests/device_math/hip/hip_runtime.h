@@ -12,6 +12,8 @@
 #define __device__
 #define __forceinline__ inline
 
+static inline uint64_t __ballot(int b) { return b != 0; }   // a wavefront of one lane
+
 static inline double bits24(double x)
 {
     if (!(std::fabs(x) < std::numeric_limits<double>::infinity())) return x;
@@ -29,13 +31,20 @@ static inline float __builtin_amdgcn_rcpf(float x) { return flush(1.0f / flush(x
 static inline float __builtin_amdgcn_rsqf(float x) { return (float)(1.0 / std::sqrt((double)flush(x))); }
 static inline float __builtin_amdgcn_sqrtf(float x) { return std::sqrt(flush(x)); }
 
-// the class mask's bits of finite nonzero values: 0x8 negative normal, 0x10
-// negative denormal, 0x80 positive denormal, 0x100 positive normal
+// the class mask's bits: 0x1 and 0x2 NaN, then from negative to positive
+// infinity -inf 0x4, normal 0x8, denormal 0x10, -0 0x20, +0 0x40 and so on
 template <class T>
 static inline bool in_class(T x, int mask)
 {
-    if (std::fpclassify(x) == FP_NORMAL) return (mask & (x > T(0) ? 0x100 : 0x8)) != 0;
-    return std::fpclassify(x) == FP_SUBNORMAL && (mask & (x > T(0) ? 0x80 : 0x10)) != 0;
+    int k;   // bits from the middle
+    switch (std::fpclassify(x)) {
+    case FP_NAN: return (mask & 0x3) != 0;
+    case FP_ZERO: k = 0; break;
+    case FP_SUBNORMAL: k = 1; break;
+    case FP_NORMAL: k = 2; break;
+    default: k = 3;
+    }
+    return (mask & (std::signbit(x) ? 0x20 >> k : 0x40 << k)) != 0;
 }
 static inline bool __builtin_amdgcn_class(double x, int mask) { return in_class(x, mask); }
 static inline bool __builtin_amdgcn_classf(float x, int mask) { return in_class(x, mask); }

@@ -112,3 +112,27 @@ def test_hllc_supersonic_with_no_fan(dm, dtype, u, p, sign):
     assert not bad and st == oracle.OK and uf == uref
     tol = 8 * np.finfo(dtype).eps   # products of three or four factors
     assert (np.abs(F - ref) <= tol * np.abs(ref)).all(), (F, ref)
+
+
+@pytest.mark.parametrize("dtype,scale", [(np.float64, 2.0 ** -560), (np.float64, 2.0 ** 500), (np.float32, 2.0 ** -80),
+                                         (np.float32, 2.0 ** 62), (np.float64, 1.0), (np.float32, 1.0)])
+def test_hllc_units(dm, dtype, scale):
+    """Densities and pressures whose product leaves the type's range."""
+    L, R = [0.25 * scale, 0.75 * scale, 0.5, 3.0 * scale, 0.25], [0.5 * scale, 1.0 * scale, 0.25, 1.5 * scale, 0.5]
+    (F, uf, bad), (ref, uref, st) = hllc(dm, dtype, L, R)
+    assert not bad and st == oracle.OK
+    tol = 16 * np.finfo(dtype).eps   # signal speeds of a few roundings, then products of three or four factors
+    assert (np.abs(F - ref) <= tol * np.abs(ref)).all() and abs(uf - uref) <= tol, (F, ref)
+
+
+@pytest.mark.parametrize("dtype", [np.float64, np.float32])
+@pytest.mark.parametrize("row,value", [(3, -2.0), (0, -2.0), (3, np.nan), (3, np.inf), (0, np.inf), (0, 0.0)])
+def test_hllc_reports_non_physical_sides(dm, dtype, row, value):
+    good, side = [0.25, 0.75, 0.5, 3.0, 0.25], [0.25, 0.75, 0.5, 3.0, 0.25]
+    side[row] = value
+    if value == 0.0:
+        side[1] = 0.0   # no density at all
+    for L, R in ((good, side), (side, good)):
+        F, uf = np.empty(5, dtype), np.empty(1, dtype)
+        f = dm.dm_hllc if dtype == np.float64 else dm.dm_hllc_f
+        assert f(_p(GAMMA), _p(PI_INF), _p(np.array(L, dtype)), _p(np.array(R, dtype)), _p(F), _p(uf))
