@@ -151,7 +151,9 @@ __device__ __forceinline__ bool tile2_char_rate(const Grid &g, const T (&pl)[6][
 
 // One variable group of a cell's stage result: rows V0 .. V0 + 2 from the
 // faces around it.  fx, fy: its low x and y faces; rx (if hx), ry (if hy):
-// characteristic rates in place of its x or y terms.
+// characteristic rates in place of its x or y terms.  The sum of a cell
+// without them is written as one fused product each, so that it is rounded
+// alike with and without the rates in the kernel.
 template <int V0, class T, class S>
 __device__ __forceinline__ void combine2(const Tile2Lds<T, S> &L, int fx, int fy, T idx, T idy, bool hx, const T *rx,
                                          bool hy, const T *ry, T hsrc, T *out)
@@ -159,18 +161,17 @@ __device__ __forceinline__ void combine2(const Tile2Lds<T, S> &L, int fx, int fy
 #pragma unroll
     for (int k = 0; k < 3; k++) {
         const int v = V0 + k;
-        T s = (L.flux[0][v][fx] - L.flux[0][v][fx + 1]) * idx;
-        if (hx) s = rx[v];
-        const T ty = (L.flux[1][v][fy] - L.flux[1][v][fy + S::TX]) * idy;
-        s += hy ? ry[v] : ty;
-        out[k] = s;
+        const T dx = L.flux[0][v][fx] - L.flux[0][v][fx + 1];
+        const T dy = L.flux[1][v][fy] - L.flux[1][v][fy + S::TX];
+        out[k] = fmaT(dx, idx, dy * idy);
+        if (hx || hy) out[k] = (hx ? rx[v] : dx * idx) + (hy ? ry[v] : dy * idy);
     }
     if constexpr (V0 + 2 == S::A) {
-        T divu = (L.flux[0][S::NV][fx + 1] - L.flux[0][S::NV][fx]) * idx;
-        if (hx) divu = T(0);
-        const T dy = (L.flux[1][S::NV][fy + S::TX] - L.flux[1][S::NV][fy]) * idy;
-        if (!hy) divu += dy;
-        out[2] += hsrc * divu;
+        const T dx = L.flux[0][S::NV][fx + 1] - L.flux[0][S::NV][fx];
+        const T dy = L.flux[1][S::NV][fy + S::TX] - L.flux[1][S::NV][fy];
+        T divu = fmaT(dx, idx, dy * idy);
+        if (hx || hy) divu = (hx ? T(0) : dx * idx) + (hy ? T(0) : dy * idy);
+        out[2] = fmaT(hsrc, divu, out[2]);
     }
 }
 
