@@ -70,6 +70,8 @@ __device__ __forceinline__ uint16_t bf16_bits(double x)
 // 182 + 120 us (x+y, z) to 160 + 104 us.
 template <class T>
 constexpr T kDivisorMax = sizeof(T) == 8 ? T(0x1p1000) : T(0x1p125f);   // below: a normal reciprocal
+template <class T>
+constexpr T kDivisorMin = sizeof(T) == 8 ? T(0x1p-900) : T(0x1p-100f);  // above: one that is finite, and normal remainders
 __device__ __forceinline__ double divisor(double s)
 {
     double r = __builtin_amdgcn_rcp(s);
@@ -257,11 +259,11 @@ __device__ __forceinline__ void features_of(const T (&d)[3][5], T sqrt_eps, uint
 #pragma unroll
         for (int j = 0; j < 5; j++) mx = maxabs(mx, d[m][j]);
         const T scale = mx > sqrt_eps ? mx : sqrt_eps;
-        if (scale < kDivisorMax<T>) {
+        if (scale < kDivisorMax<T> && sqrt_eps >= kDivisorMin<T>) {   // scale >= sqrt_eps, the same for all threads
             const T r = divisor(scale);
 #pragma unroll
             for (int j = 0; j < 5; j++) out[5 * m + j] = bf16_bits(quotient(d[m][j], scale, r));
-        } else {   // overflowed differences
+        } else {   // overflowed differences, or an epsilon whose root FP32 holds as a denormal
 #pragma unroll
             for (int j = 0; j < 5; j++) out[5 * m + j] = bf16_bits(d[m][j] / scale);
         }

@@ -4,6 +4,7 @@ bias counts: thresholds just below and just above its P(smooth) of zero
 features give the all-linear and the all-WENO5 right-hand side, and a single
 cell with another volume fraction, density or pressure alone takes the
 network's own decisions, as the oracle's."""
+import dataclasses
 import sys
 
 import numpy as np
@@ -107,3 +108,16 @@ def test_one_cell_that_differs(n, kernel, bump, precision):
     got = routed(spec, q, kernel, precision, net, tau).double().cpu().numpy()
     err = rhs_err(got, ref, q, spec)
     assert err.max() <= bar, err
+
+
+@pytest.mark.parametrize("n,kernel", GRIDS)
+def test_small_weno_eps_in_fp32(n, kernel):
+    """The floor of the features' divisor, sqrt(weno_eps), below FP32's normal
+    numbers: zero differences still give zero features."""
+    print(f"[zero logit] {n} kernel {kernel} eps 1e-80", file=sys.stderr, flush=True)
+    net = network()
+    spec, q = state(n)
+    spec = dataclasses.replace(spec, weno_eps=1e-80)
+    p0 = p_zero(net)
+    linear = routed(state(n)[0], q, kernel, mfc.MFC_FP32_MIXED, net, 0.0)   # no epsilon in it
+    assert torch.equal(routed(spec, q, kernel, mfc.MFC_FP32_MIXED, net, p0 - 1e-5), linear)
