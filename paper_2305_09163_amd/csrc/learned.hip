@@ -612,13 +612,16 @@ int mfc_set_indicator(mfc_grid *h, const float *params_host, double tau)
     if (!std::isfinite(tau)) return fail(MFC_E_ARG, "tau must be finite");
     for (int i = 0; i < NPARAM; i++)
         if (!std::isfinite(params_host[i])) return fail(MFC_E_ARG, "non-finite network parameter");
-    hipError_t e = hipSuccess;
-    if (!h->mlp) e = hipMalloc((void **)&h->mlp, kRoutedWords * sizeof(float));
+    hipError_t e = hipSetDevice(h->device);
+    if (e == hipSuccess && !h->mlp) e = hipMalloc((void **)&h->mlp, kRoutedWords * sizeof(float));
     if (e == hipSuccess) e = hipMemcpy(h->mlp, params_host, NPARAM * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_zero_logit, dim3(1), dim3(kThreads), 0, 0, h->mlp);
-        e = hipDeviceSynchronize();   // before work of any stream that reads it
+        // waited for before work of any stream reads it, on its own stream
+        // only: other streams' work goes on
+        hipLaunchKernelGGL(k_zero_logit, dim3(1), dim3(kThreads), 0, nullptr, h->mlp);
+        e = hipGetLastError();
     }
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) return hip_status(e, "indicator upload");
     // P > tau  <=>  logit > log(tau / (1 - tau))
     h->logit_tau = tau <= 0.0 ? -INFINITY : (tau >= 1.0 ? INFINITY : (float)std::log(tau / (1.0 - tau)));
