@@ -37,6 +37,7 @@
 // one takes the linear fifth-order stencil for every variable instead of
 // WENO5.  ORDER selects the reconstruction otherwise (5 WENO5, 3 WENO3,
 // 1 first order; the routed variant is always 5).
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -967,13 +968,14 @@ int64_t split_z_partials(const Grid &g)
 // 13.5 us, 64^3 35.0 -> 26.3, 96 x 80 x 72 47.2 -> 47.0, 128^3 138.1 with four
 // (139 with two, 147 with one), FP32 256^3 584 with four (605, 640).
 //
-// Neither choice changes a cell's arithmetic.  Chunks are kept long enough
-// for the launch's z extent (65535).
+// Neither choice changes a cell's arithmetic.  Both are kept long enough for
+// the launch's z extent (65535): nz goes up to 2^20.
 void split_chunks(Grid &g, bool fp32)
 {
     const int nz = g.n[2];
     const int64_t tiles = (int64_t)((g.n[0] + TX - 1) / TX) * ((g.n[1] + TY - 1) / TY) * nz;
-    g.xy_planes = nz > 65535 ? 4 : (tiles < 4 * 768 ? 1 : (tiles < 10240 ? 2 : 4));
+    const int least = (nz + 65534) / 65535;
+    g.xy_planes = std::max(least, least > 1 ? 4 : (tiles < 4 * 768 ? 1 : (tiles < 10240 ? 2 : 4)));
     const int64_t cols = ((int64_t)g.n[0] * g.n[1] + kNZT - 1) / kNZT;
     double best = 1e300;
     for (int lz = 1; lz <= 32; lz++) {
