@@ -134,12 +134,17 @@ def _check(status: int, call: str):
 
 def _stream(stream=None):
     """HIP stream handle: the given torch stream's, or the current one's.  The
-    current handle is asked for directly: a torch stream object takes 3.4 us
-    to make, a third of a training step's host time, and the raw query 0.3."""
+    current handle is asked for directly where torch has that query: a torch
+    stream object takes 3.4 us to make, a third of a training step's host
+    time, and the raw query 0.3."""
     if stream is not None:
         return _VP(stream.cuda_stream)
     import torch
-    return _VP(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
+    C = torch._C
+    try:
+        return _VP(C._cuda_getCurrentRawStream(C._cuda_getDevice()))
+    except AttributeError:
+        return _VP(torch.cuda.current_stream().cuda_stream)
 
 
 def _ptr(t):
