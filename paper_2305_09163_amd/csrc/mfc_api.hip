@@ -386,7 +386,10 @@ int rhs_dispatch(mfc_grid *h, const void *q, const void *q0, void *out, int mode
     int st;
     if (h->desc.kernel == MFC_KERNEL_STAGED) st = launch_rhs_staged(h, q, q0, out, mode, dt, dt_dev, s);
     else if (h->desc.kernel == MFC_KERNEL_SPLIT) st = launch_rhs_split(h, q, q0, out, mode, dt, dt_dev, s, cfl, zmax);
-    else if (h->desc.ndim == 2) st = launch_rhs_plane(h, q, q0, out, mode, StepSize{}, s);   // mode 0
+    else if (h->desc.ndim == 2) {   // stages set their step size themselves (rk3_step_tiles)
+        if (mode != 0) return fail(MFC_E_UNSUPPORTED, "a 2D stage outside its step");
+        st = launch_rhs_plane(h, q, q0, out, mode, StepSize{}, s);
+    }
     else st = launch_rhs_fused(h, q, q0, out, mode, dt, dt_dev, s);
     // with characteristic faces, a wave-speed-reducing last stage leaves the
     // z faces' cells to the boundary pass, whose maxima follow the z kernel's
