@@ -114,7 +114,10 @@ typedef struct {
     int recon;           /* MFC_RECON_*: WENO5, WENO3 or FIRST_ORDER (every kernel),
                             or LEARNED (fused and split kernels; needs
                             mfc_set_indicator before any right-hand side)          */
-    double weno_eps;     /* WENO5-JS epsilon, > 0 (1e-6 in the paper's setting)    */
+    double weno_eps;     /* WENO epsilon, > 0 (1e-6 in the paper's setting).  One
+                            below what uniform cells' products hold is taken
+                            as that: 2.4e-38 for WENO5 and in FP32, 5.5e-76
+                            for WENO3                                       */
     int kernel;          /* MFC_KERNEL_*                                           */
     int model;           /* MFC_MODEL_ALLAIRE or MFC_MODEL_KAPILA                  */
     const double *faces[3];  /* non-uniform cells (Sec. 4.1): host array of the

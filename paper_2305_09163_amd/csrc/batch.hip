@@ -447,7 +447,8 @@ int mfc_batch_init(const mfc_grid_desc *descs, int count, mfc_batch **out)
         g.g2 = 1.0 / (d.gamma[1] - 1.0);
         g.h1 = d.gamma[0] * d.pi_inf[0] / (d.gamma[0] - 1.0);
         g.h2 = d.gamma[1] * d.pi_inf[1] / (d.gamma[1] - 1.0);
-        g.eps = d.weno_eps;
+        g.weno_eps = d.weno_eps;
+        g.eps = usable_eps(d.weno_eps, false, d.precision == MFC_FP32_MIXED, false);
         set_kapila(g, d);
         g.order = 5;
         g.stretched = 0;

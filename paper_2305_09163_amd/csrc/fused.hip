@@ -369,7 +369,7 @@ int rhs_fused(mfc_grid *h, const T *q, const T *q0, T *out, int mode, double dt,
     const Grid &g = h->g;
     dim3 grid((g.n[0] + S::TX - 1) / S::TX, NDIM >= 2 ? (g.n[1] + S::TY - 1) / S::TY : 1,
               NDIM == 3 ? (g.n[2] + kLZ - 1) / kLZ : 1);
-    const T se = T(__builtin_sqrt(g.eps));
+    const T se = T(__builtin_sqrt(g.weno_eps));
     timing_begin(h, s);
     hipLaunchKernelGGL((k_fused<NDIM, T, ROUTE, ORDER, STRETCH>), grid, dim3(S::NT), 0, s, g, q, q0, out, mode, dt, dt_dev, h->flag, kLZ,
                        h->mlp, h->logit_tau, se);

@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(kThreads, 3)
             double st[5];
 #pragma unroll
             for (int j = 0; j < 5; j++) st[j] = v == E ? pr[j] : s_w[v][at[j]];
-            dev = fmax(dev, weno_deviation(st, g.eps, rare));
+            dev = fmax(dev, weno_deviation(st, g.weno_eps, rare));
         }
         if (__builtin_expect(rare, 0)) {
             dev = 0.0;
@@ -220,7 +220,7 @@ __global__ void __launch_bounds__(kThreads, 3)
                 double st[5];
 #pragma unroll
                 for (int j = 0; j < 5; j++) st[j] = v == E ? pr[j] : s_w[v][at[j]];
-                dev = fmax(dev, weno_deviation<true>(st, g.eps, rare));
+                dev = fmax(dev, weno_deviation<true>(st, g.weno_eps, rare));
             }
         }
         Y[t] = dev < threshold ? 1 : 0;
@@ -472,7 +472,7 @@ int mfc_harvest(mfc_grid *h, void *q, uint16_t *features, uint8_t *labels, doubl
     int st = mfc_fill_ghosts(h, q, stream);
     if (st) return st;
     hipStream_t s = (hipStream_t)stream;
-    const double se = std::sqrt(h->g.eps), *qd = (const double *)q;
+    const double se = std::sqrt(h->g.weno_eps), *qd = (const double *)q;
     auto launch = [&](auto nd) {
         using S = HarvestTile<decltype(nd)::value>;
         const Grid &g = h->g;

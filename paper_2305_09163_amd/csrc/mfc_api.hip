@@ -83,7 +83,10 @@ void make_grid(const mfc_grid_desc &desc, Grid &g)
     g.g2 = 1.0 / (desc.gamma[1] - 1.0);
     g.h1 = desc.gamma[0] * desc.pi_inf[0] / (desc.gamma[0] - 1.0);
     g.h2 = desc.gamma[1] * desc.pi_inf[1] / (desc.gamma[1] - 1.0);
-    g.eps = desc.weno_eps;
+    bool nonuniform = true;   // every dimension
+    for (int d = 0; d < desc.ndim; d++) nonuniform &= desc.faces[d] != nullptr;
+    g.weno_eps = desc.weno_eps;
+    g.eps = usable_eps(desc.weno_eps, desc.recon == MFC_RECON_WENO3, desc.precision == MFC_FP32_MIXED, nonuniform);
     set_kapila(g, desc);
     g.order = desc.recon == MFC_RECON_WENO3 ? 3 : (desc.recon == MFC_RECON_FIRST_ORDER ? 1 : 5);
     if (g.ndim == 3) split_chunks(g, desc.precision == MFC_FP32_MIXED);

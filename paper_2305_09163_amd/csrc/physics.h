@@ -36,7 +36,8 @@ struct Grid {
     double dxmin;
     // mixture EOS coefficients: Gamma = a1*g1 + (1-a1)*g2, Pi = a1*h1 + (1-a1)*h2
     double g1, g2, h1, h2;
-    double eps;       // WENO epsilon
+    double eps;       // WENO epsilon of the reconstructions (no smaller than their products hold)
+    double weno_eps;  // the caller's (the indicator's features and labels)
     int bc[6];        // boundary kind per face (x-, x+, y-, y+, z-, z+): MFC_BC_*
     int xy_planes, z_planes;  // 3D: planes per workgroup of the split path's two kernels
     int order;        // reconstruction of the staged path: 5 WENO5, 3 WENO3, 1 first order
@@ -330,6 +331,18 @@ __device__ __forceinline__ T alpha_source(const Grid &g, T alpha1, T p)
 //     (0 .. 1e9) the largest error is 2.7e-7 of the stencil's scale (3.0e-7
 //     relative to the smallest), the mean the same or smaller on each.
 // Ideal weights are scaled by 10: (1, 6, 3) at x_{i+1/2}, (3, 6, 1) at x_{i-1/2}.
+//
+// In a uniform region eps is all there is of an indicator, and the products
+// above must be normal numbers: FP64's eighth power in WENO5, its fourth in
+// WENO3, FP32's own range.  The host raises a smaller one to that; it would
+// only tell differences apart that are smaller than its root.  Non-uniform
+// FP64 cells have another form for it (weno5_nonuniform_pair).
+inline double usable_eps(double eps, bool weno3, bool fp32, bool nonuniform)
+{
+    if (nonuniform && !fp32) return eps;
+    const double least = weno3 && !fp32 ? 0x1p-250 : 0x1p-125;
+    return eps > least ? eps : least;
+}
 __device__ __forceinline__ void weno5_pair(double vm2, double vm1, double v0, double vp1, double vp2,
                                            double eps, double &plus, double &minus)
 {

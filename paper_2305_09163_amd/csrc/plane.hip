@@ -70,7 +70,7 @@ int rhs_plane(mfc_grid *h, const void *q, const void *q0, void *out, int mode, c
     timing_begin(h, s);
     hipLaunchKernelGGL((k_plane<T, ROUTE, ORDER, STRETCH>), dim3((unsigned)tiles), dim3(S2::NT), 0, s, g, (const T *)q,
                        (const T *)q0, (T *)out, mode, ss, tiles_x, h->flag, h->mlp, h->logit_tau,
-                       T(__builtin_sqrt(g.eps)));
+                       T(__builtin_sqrt(g.weno_eps)));
     timing_end(h, s);
     return hip_status(hipGetLastError(), "2D right-hand side launch");
 }

@@ -870,7 +870,7 @@ int rhs_split(mfc_grid *h, const T *q, const T *q0, T *out, int mode, double dt,
     const dim3 gxy = xy_grid(g);
     const dim3 gz = z_grid(g);
     T *lxy = (T *)h->lxy;
-    const T se = T(__builtin_sqrt(g.eps));
+    const T se = T(__builtin_sqrt(g.weno_eps));
     double *partial = cfl > 0.0 ? h->partial : nullptr;
     // the x+y pass forms its part of the stage combination whenever the
     // stage's dt is known before it runs (not in a first stage whose dt is
@@ -909,7 +909,7 @@ int rhs_split_raw(const Grid &g, const T *q, T *out, T *lxy, int *flag, hipStrea
 {
     const dim3 gxy = xy_grid(g);
     const dim3 gz = z_grid(g);
-    const T se = T(__builtin_sqrt(g.eps));
+    const T se = T(__builtin_sqrt(g.weno_eps));
     hipLaunchKernelGGL((k_xy<T, false, ORDER, false, false>), gxy, dim3(NT), 0, s, g, q, q, lxy, flag, nullptr, 0.f,
                        se, nullptr, 0, 0, 0.0, nullptr);
     hipLaunchKernelGGL((k_z<T, false, ORDER, false, false, false>), gz, dim3(kNZT), 0, s, g, q, out, lxy, 0, 0.0,

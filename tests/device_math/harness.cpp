@@ -17,9 +17,22 @@ void dm_weno5_nonuniform_f(const double *row, const float *s, float eps, float *
     weno5_nonuniform_pair<float>(row, s[0], s[1], s[2], s[3], s[4], eps, *plus, *minus);
 }
 
+// Uniform cells, the epsilon as the host passes it on.
+void dm_weno5(const double *s, double eps, double *plus, double *minus)
+{
+    weno5_pair(s[0], s[1], s[2], s[3], s[4], usable_eps(eps, false, false, false), *plus, *minus);
+}
+void dm_weno3(const double *s, double eps, double *plus, double *minus)
+{
+    weno3_pair(s[0], s[1], s[2], usable_eps(eps, true, false, false), *plus, *minus);
+}
+void dm_weno3_f(const float *s, float eps, float *plus, float *minus)
+{
+    weno3_pair(s[0], s[1], s[2], (float)usable_eps(eps, true, true, false), *plus, *minus);
+}
 void dm_weno5_f(const float *s, float eps, float *plus, float *minus)
 {
-    weno5_pair(s[0], s[1], s[2], s[3], s[4], eps, *plus, *minus);
+    weno5_pair(s[0], s[1], s[2], s[3], s[4], (float)usable_eps(eps, false, true, false), *plus, *minus);
 }
 
 }  // extern "C"

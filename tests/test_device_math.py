@@ -68,6 +68,21 @@ def test_weno5_nonuniform_fp64(dm, name, eps):
     assert abs(plus[0] - ref[0]) <= tol and abs(minus[0] - ref[1]) <= tol, (plus, minus, ref)
 
 
+@pytest.mark.parametrize("order,dtype", [(5, np.float64), (5, np.float32), (3, np.float64), (3, np.float32)])
+@pytest.mark.parametrize("eps", [1e-6, 1e-37, 1e-40, 1e-100, 1e-150])
+@pytest.mark.parametrize("name", ["constant", "smooth", "jump", "far jump"])
+def test_small_eps_on_uniform_cells(dm, name, eps, order, dtype):
+    """An epsilon below what the products can hold: differences of FP32 or
+    FP64 values of order one are far above its root, or zero."""
+    s = np.array(STENCILS[name][:5] if order == 5 else STENCILS[name][1:4], dtype)
+    plus, minus = np.empty(1, dtype), np.empty(1, dtype)
+    f = getattr(dm, f"dm_weno{order}" + ("" if dtype == np.float64 else "_f"))
+    f(_p(s), (ctypes.c_double if dtype == np.float64 else ctypes.c_float)(eps), _p(plus), _p(minus))
+    ref = (oracle.weno5 if order == 5 else oracle.weno3)(s.astype(float), eps)
+    tol = 64 * np.finfo(dtype).eps * np.abs(s).max()
+    assert abs(plus[0] - ref[0]) <= tol and abs(minus[0] - ref[1]) <= tol, (plus, minus, ref)
+
+
 @pytest.mark.parametrize("uniform", [True, False])
 @pytest.mark.parametrize("s", [(1, 1, 1, 1e20, 1e20), (1e20, 1e20, 1, 1, 1), (1, 1, 1, 1, 1e25), (1e25, 1, 1, 1, 1),
                                (1, 1.5, 2, 1e22, 3e22), (3e22, 1e22, 2, 1.5, 1), (1, 1, 1, 2e19, 1), (1, 1.5, 2, 1e9, 1e9),
