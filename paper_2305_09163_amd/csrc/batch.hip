@@ -30,8 +30,11 @@ namespace mfc {
 namespace {
 
 constexpr int kBT = 256;          // threads per workgroup
-// wave-speed workgroups per run (64 runs of 64 .. 512 cells a side in FP32: 36 us; with 8, 102)
-constexpr int kWsBlocks = 64;
+// Wave-speed workgroups of a run: one per 256 cells, at most 64.  A step of
+// 1000 runs of 16 x 16 cells in FP64 takes 111 us (166 with 64 for every run,
+// 115 with one per 4096 cells), of 8 runs of 64 x 64 28 (37 with one per 4096);
+// of 64 runs of 64 .. 512 cells a side 1140 (1595 with 8 for every run).
+constexpr int kWsCells = 256, kWsMost = 64;
 constexpr int kXcds = 8;          // accelerator complex dies of the MI355X
 
 template <class T>
@@ -43,17 +46,18 @@ struct RunDev {
 
 // ------------------------------------------------------------ wave speed
 template <class T>
-__global__ void __launch_bounds__(kBT) k_batch_wavespeed(const RunDev<T> *__restrict__ runs, double *__restrict__ partial,
-                                                         int *__restrict__ flag)
+__global__ void __launch_bounds__(kBT) k_batch_wavespeed(const RunDev<T> *__restrict__ runs,
+                                                         const int *__restrict__ block_run, const int *__restrict__ first,
+                                                         double *__restrict__ partial, int *__restrict__ flag)
 {
     __shared__ double red[kBT / 64];
-    const int run = blockIdx.x / kWsBlocks, part = blockIdx.x % kWsBlocks;
+    const int run = block_run[blockIdx.x], part = (int)blockIdx.x - first[run], parts = first[run + 1] - first[run];
     const RunDev<T> &R = runs[run];
     const Grid &g = R.g;
     const int64_t total = (int64_t)g.n[0] * g.n[1];
     double smax = 0.0;
     bool bad = false;
-    for (int64_t t = (int64_t)part * kBT + threadIdx.x; t < total; t += (int64_t)kWsBlocks * kBT) {
+    for (int64_t t = (int64_t)part * kBT + threadIdx.x; t < total; t += (int64_t)parts * kBT) {
         const int i = (int)(t % g.n[0]), j = (int)(t / g.n[0]);
         const int64_t c = (int64_t)(j + NG) * g.stride[1] + (i + NG);
         T qc[6], wc[6];
@@ -78,24 +82,19 @@ __global__ void __launch_bounds__(kBT) k_batch_wavespeed(const RunDev<T> *__rest
 }
 
 // Per-run step size and accumulated time: scal[3 r + 0..2] = smax, dt, t, one
-// workgroup per run.  The maximum comes from run r's wave-speed partials, or
-// (carried) from those that the previous step's last stage left for its items,
-// first[r] .. first[r + 1] - 1, kItemSpeeds per item.
+// workgroup per run.  The maximum comes from run r's wave-speed workgroups,
+// first[r] .. first[r + 1] - 1, one each, or from the items of the previous
+// step's last stage, kItemSpeeds each.
 constexpr int kItemSpeeds = 4;
-__global__ void __launch_bounds__(kBT) k_batch_dt(const double *__restrict__ partial, const double *__restrict__ carried,
-                                                  const int *__restrict__ first, double *__restrict__ scal,
-                                                  const double *__restrict__ dxmin, double cfl)
+__global__ void __launch_bounds__(kBT) k_batch_dt(const double *__restrict__ speeds, int each, const int *__restrict__ first,
+                                                  double *__restrict__ scal, const double *__restrict__ dxmin, double cfl)
 {
     __shared__ double red[kBT / 64];
     const int r = blockIdx.x;
     double m = 0.0;
-    if (carried) {
-        const int end = kItemSpeeds * first[r + 1];
+    const int end = each * first[r + 1];
 #pragma unroll 8
-        for (int b = kItemSpeeds * first[r] + threadIdx.x; b < end; b += kBT) m = __builtin_fmax(m, carried[b]);
-    } else if (threadIdx.x < kWsBlocks) {
-        m = partial[r * kWsBlocks + threadIdx.x];
-    }
+    for (int b = each * first[r] + threadIdx.x; b < end; b += kBT) m = __builtin_fmax(m, speeds[b]);
     m = wave_max(m);
     if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = m;
     __syncthreads();
@@ -205,7 +204,9 @@ struct mfc_batch {
     int64_t cells = 0;
     int *items[kNumShapes][2] = {};   // item_run, item_tile per shape (device)
     int nitems[kNumShapes] = {};
-    double *partial = nullptr;        // [nrun * kWsBlocks]
+    double *partial = nullptr;        // wave-speed maxima, one per workgroup
+    int *ws_run = nullptr, *ws_first = nullptr;   // run of a wave-speed workgroup, [nrun + 1] first of a run (device)
+    int ws_blocks = 0;
     double *speeds = nullptr;         // [kItemSpeeds * items] carried wave-speed maxima
     int *first[kNumShapes] = {};      // [nrun + 1] first item of a run, per shape (device)
     double *scal = nullptr;           // [3 * nrun]
@@ -312,10 +313,11 @@ int enqueue_step(mfc_batch *b, double cfl, hipStream_t s, bool carried_in, bool 
 {
     const RunDev<T> *runs = (const RunDev<T> *)b->runs;
     if (!carried_in)
-        hipLaunchKernelGGL((k_batch_wavespeed<T>), dim3(b->nrun * kWsBlocks), dim3(kBT), 0, s, runs, b->partial,
-                           b->flag);
-    hipLaunchKernelGGL(k_batch_dt, dim3(b->nrun), dim3(kBT), 0, s, b->partial, carried_in ? b->speeds : nullptr,
-                       b->first[b->tune.shape], b->scal, b->dxmin, cfl);
+        hipLaunchKernelGGL((k_batch_wavespeed<T>), dim3(b->ws_blocks), dim3(kBT), 0, s, runs, b->ws_run, b->ws_first,
+                           b->partial, b->flag);
+    hipLaunchKernelGGL(k_batch_dt, dim3(b->nrun), dim3(kBT), 0, s, carried_in ? b->speeds : b->partial,
+                       carried_in ? kItemSpeeds : 1, carried_in ? b->first[b->tune.shape] : b->ws_first, b->scal, b->dxmin,
+                       cfl);
     launch_stage<T>(b, 1, s);
     launch_stage<T>(b, 2, s);
     launch_stage<T>(b, 3, s, carry_out ? b->speeds : nullptr);
@@ -371,7 +373,7 @@ int mfc_batch_free(mfc_batch *b)
     for (int sh = 0; sh < kNumShapes; sh++)
         for (int k = 0; k < 2; k++)
             if (b->items[sh][k]) (void)hipFree(b->items[sh][k]);
-    for (int *p : b->first)
+    for (int *p : {b->first[0], b->first[1], b->first[2], b->ws_run, b->ws_first})
         if (p) (void)hipFree(p);
     for (void *p : {b->runs, (void *)b->speeds, (void *)b->partial, (void *)b->scal, (void *)b->dxmin, (void *)b->flag})
         if (p) (void)hipFree(p);
@@ -465,7 +467,21 @@ int mfc_batch_init(const mfc_grid_desc *descs, int count, mfc_batch **out)
     for (int r = 0; r < count; r++)
         for (int k = 0; k < 2; k++) alloc(&b->stage[2 * r + k], (size_t)6 * b->grids[r].vstride * elem(b));
     alloc(&b->runs, sizeof(RunDev<double>) * count);
-    alloc((void **)&b->partial, sizeof(double) * count * kWsBlocks);
+    {
+        std::vector<int> run, first;
+        for (int r = 0; r < count; r++) {
+            first.push_back((int)run.size());
+            const int64_t cells = (int64_t)b->grids[r].n[0] * b->grids[r].n[1];
+            run.insert(run.end(), (size_t)std::min<int64_t>((cells + kWsCells - 1) / kWsCells, kWsMost), r);
+        }
+        b->ws_blocks = (int)run.size();
+        first.push_back(b->ws_blocks);
+        alloc((void **)&b->ws_run, sizeof(int) * run.size());
+        alloc((void **)&b->ws_first, sizeof(int) * first.size());
+        if (e == hipSuccess) e = hipMemcpy(b->ws_run, run.data(), sizeof(int) * run.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(b->ws_first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice);
+    }
+    alloc((void **)&b->partial, sizeof(double) * b->ws_blocks);
     alloc((void **)&b->scal, sizeof(double) * 3 * count);
     alloc((void **)&b->dxmin, sizeof(double) * count);
     alloc((void **)&b->flag, sizeof(int) * 2);
