@@ -250,10 +250,18 @@ int64_t line_partials(const Grid &g) { return 2 * line_partials_half(g); }
 // characteristic faces, whose boundary pass follows every stage, nor the
 // timing of single right-hand sides; a lone step of a long grid would need a
 // copy back.
+//   A lone step of up to 1022 cells is one workgroup of up to 1024 threads,
+// whose 128 registers each spill (FP64 WENO5 24, which costs little: 1022 cells
+// 22 us against 37 of the launches per stage; 62 on non-uniform cells, FP32
+// there 24).  Non-uniform WENO5 cells pass the launches, 47 us FP64 and 45
+// FP32, at 638 and 702 cells (50 and 46; 574 and 638: 46 and 43; 1022: 71 and
+// 61), so a lone step of more than 574 or 638 takes those.
 bool takes_line(const mfc_grid *h, int nsteps)
 {
+    const bool coefficients = h->g.stretched && h->desc.recon == MFC_RECON_WENO5;
+    const int lone = coefficients ? (h->desc.precision == MFC_FP64 ? 574 : 638) : kLineMax;
     return h->desc.kernel == MFC_KERNEL_FUSED && h->desc.ndim == 1 && h->desc.recon != MFC_RECON_LEARNED &&
-           !has_cbc(h) && !h->timing && (h->g.n[0] <= kLineMax || nsteps > 1);
+           !has_cbc(h) && !h->timing && (nsteps > 1 || h->g.n[0] <= lone);
 }
 
 int run_line(mfc_grid *h, void *q, int nsteps, double cfl, double dt, double *dt_out, hipStream_t s)
