@@ -174,8 +174,9 @@ __global__ void __launch_bounds__(kThreads, 3)
     if (x >= g.n[0] || y >= g.n[1] || z >= g.n[2]) return;
     const int64_t c = ((int64_t)z * g.n[1] + y) * g.n[0] + x;
     const int p = tid;
+    const int d0 = gridDim.y > 1 ? (int)blockIdx.y : 0, d1 = gridDim.y > 1 ? d0 + 1 : NDIM;   // one direction, or all
 #pragma unroll 1
-    for (int d = 0; d < NDIM; d++) {
+    for (int d = d0; d < d1; d++) {
         const int64_t t = d * cells + c;
         int at[5];   // the stencil's positions
 #pragma unroll
@@ -478,8 +479,12 @@ int mfc_harvest(mfc_grid *h, void *q, uint16_t *features, uint8_t *labels, doubl
         const Grid &g = h->g;
         const int64_t tiles = (int64_t)((g.n[0] + S::TX - 1) / S::TX) * ((g.n[1] + S::TY - 1) / S::TY) *
                               ((g.n[2] + S::TZ - 1) / S::TZ);
-        hipLaunchKernelGGL(k_harvest<decltype(nd)::value>, dim3((unsigned)tiles), dim3(kThreads), 0, s, g, qd, features, labels, maxdev,
-                           se, 0.01, h->cells);
+        // few tiles: a workgroup per direction (their conversions formed again),
+        // where one would walk them one after the other on an idle chip (8^3
+        // cells with the ghost fill 20.1 -> 16.8 us, 24^3 21.2 -> 18.0)
+        const unsigned split = tiles * decltype(nd)::value <= h->cu_count ? decltype(nd)::value : 1;
+        hipLaunchKernelGGL(k_harvest<decltype(nd)::value>, dim3((unsigned)tiles, split), dim3(kThreads), 0, s, g, qd, features,
+                           labels, maxdev, se, 0.01, h->cells);
     };
     if (h->g.ndim == 1) launch(std::integral_constant<int, 1>{});
     else if (h->g.ndim == 2) launch(std::integral_constant<int, 2>{});
