@@ -15,7 +15,7 @@
 // Neighbours past a face are read through the boundary rule (bc_cell: the
 // values a ghost fill would write, bit for bit).
 //
-// Ten steps FP64: 400 cells 84 us (the launches of before: 295), 250 cells 61
+// Ten steps FP64: 400 cells 82 us (the launches of before: 295), 250 cells 61
 // (272), 4000 cells in pieces 100 (313).  Bound by the chain of one stage, 2.0
 // us of 250 cells on the four SIMDs of one CU, 2.8 us of 400; beyond 512
 // threads a workgroup's wavefronts queue on its CU and pieces, at 9.7 us a step

@@ -441,8 +441,8 @@ __device__ __forceinline__ void recon_pair(T vm2, T vm1, T v0, T vp1, T vp2, T e
 // are two products with its divided differences, beta_r = a1^2 + a2^2 (the
 // row's a2 carries sqrt(13/3)), ideal weights per face (the increments carry
 // theirs).  Through common denominators in FP64 and relative to the central
-// stencil in FP32, as weno5_pair: 59 instructions and one reciprocal per value
-// in FP64 (values instead of increments and a reciprocal per weight: 80 and
+// stencil in FP32, as weno5_pair: 59 instructions, one reciprocal and the test
+// of its range per value in FP64 (values instead of increments and a reciprocal per weight: 80 and
 // five).  The one reciprocal is of an eighth power of the smoothness
 // indicators; where that leaves the normal numbers (an epsilon below 1e-38 in
 // a uniform region, indicators above 1e38) every weight takes its own, of a

@@ -210,7 +210,7 @@ constexpr int kXYWaves = ROUTE ? 2
 // and reads the increments' twelve per variable: 225 us for the x+y pass of
 // 128^3 cells (all 30 held: 324 with 39 registers spilled; all read per
 // variable: 287; 42 coefficients of values instead of differences: 318), in
-// 16-byte reads (269 us in 8-byte ones).  FP32 has no registers for them at
+// 16-byte reads (269 us in 8-byte ones); 229 since the weights test their range.  FP32 has no registers for them at
 // four workgroups per CU.
 template <class T>
 struct RowHeld {
@@ -958,15 +958,18 @@ int64_t split_z_partials(const Grid &g)
 // or 1 + 0.7 k us (FP32) with k workgroups per CU, k = W / 256 for W
 // workgroups, rounded up while the launch is a few rounds (a last partial
 // round costs a whole one).  The chunk that minimises the product is within
-// 4 % of the best of a sweep of 1 .. 32 planes on every size tried; against
-// the 16 planes that suit 128^3 (FP64): 36 x 34 x 33 35.0 -> 10.7 us (1
-// plane), 64^3 38.8 -> 18.5 (4), 100 x 75 x 61 40.0 -> 27.2 (4), 112^3
-// 63.2 -> 57.9 (8), 128^3 78.2 (16); FP32 256^3 364 -> 341 (32).
+// 4 % of the best of a sweep over 1, 2, 4, 6, 8, 12, 16, 24 and 32 planes on
+// every size tried; against the 16 planes that suit 128^3 (FP64):
+// 36 x 34 x 33 34.4 -> 10.8 us (1 plane), 64^3 38.6 -> 18.9 (4), 96 x 80 x 72
+// 40.8 -> 28.9 (9), 100 x 75 x 61 39.4 -> 26.6 (8; with 4 the same), 112^3
+// 63.0 -> 52.8 (12), 128^3 78.1 (16); FP32 256^3 363 -> 338 (32).
 //
 // x+y pass: one plane per workgroup below four rounds of the 768 resident
-// workgroups, two below 10240 plane tiles, else four: 36 x 34 x 33 24.5 ->
-// 13.5 us, 64^3 35.0 -> 26.3, 96 x 80 x 72 47.2 -> 47.0, 128^3 138.1 with four
-// (139 with two, 147 with one), FP32 256^3 584 with four (605, 640).
+// workgroups, two below 10240 plane tiles, else four.  In us with 1, 2, 3 and
+// 4 planes: 36 x 34 x 33 12.6, 14.7, 18.7, 23.5; 64^3 22.4, 25.4, 26.6, 32.3;
+// 100 x 75 x 61 40.3, 42.6, 44.0, 43.7; 96 x 80 x 72 45.0, 44.2, 45.7, 45.5;
+// 112^3 97.1, 94.1, 95.3, 90.8; 128^3 145.6, 136.3, 138.5, 137.8; FP32 256^3
+// 631, 603, 590, 582.
 //
 // Neither choice changes a cell's arithmetic.  Both are kept long enough for
 // the launch's z extent (65535): nz goes up to 2^20.

@@ -19,7 +19,7 @@
 // single pass: a 16 x 16 tile's 288 reconstructions took two passes of 256
 // threads, the second one-eighth full.
 //
-// 253 x 181 cells FP64 (234 tiles): 8.0 us a launch, 11.5 with one sweep after
+// 253 x 181 cells FP64 (208 tiles): 8.0 us a launch, 11.5 with one sweep after
 // the other on 256 threads.  30285 tiles of the 64 .. 512 ensemble in FP32:
 // 286 us a launch, 332 so (about 800 issue slots per wavefront and tile: within
 // a few percent of the card's issue rate).
