@@ -72,11 +72,11 @@ KERNEL_TIMING_STRIDE = 10
 # only for the kernel sources they were taken on; any change to those files
 # turns `traffic` back to null.
 TRAFFIC_SOURCES = ("split.hip", "physics.h", "internal.h", "charbc.h")
-TRAFFIC = {"sha256": "bcb207b46f1a439ca8171579f25553c3850d1683b220d2d12bbe837ebbe5d77d",
-           ("split", "fp32", 128, 0): (126.15e6, 62.40e6),
-           ("split", "fp32", 128, 1): (143.65e6, 61.50e6),
-           ("split", "fp64", 128, 0): (242.79e6, 127.68e6),
-           ("split", "fp64", 128, 1): (288.31e6, 123.55e6)}
+TRAFFIC = {"sha256": "408c51c59004d790b4b6828a19798d7c85298f8c66969dc83ff196cdb511708e",
+           ("split", "fp32", 128, 0): (126.70e6, 62.06e6),
+           ("split", "fp32", 128, 1): (164.72e6, 61.64e6),
+           ("split", "fp64", 128, 0): (237.06e6, 122.38e6),
+           ("split", "fp64", 128, 1): (287.59e6, 123.14e6)}
 PEAK_FP64_VALU = 78.6e12      # 256 CU x 2.4 GHz x 128 FP64 flop/clk/CU
 PEAK_FP32_VALU = 157.3e12
 PEAK_HBM = 8.0e12
